@@ -725,7 +725,7 @@ k_zpass(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R>::t
   const int j = t % M0;
   const int p = t / M0;
   const int line = blockIdx.x * P + p;
-  const bool line_ok = line < Z::LINES;
+  const bool line_ok = Z::LINES % P == 0 || line < Z::LINES;
   V v[Q][R0];
   // collapse epilogue: the running maximum of this thread's points, fetched with the inputs so
   // that its latency hides behind the transforms
