@@ -79,7 +79,9 @@ typedef struct {
 /* Whether N is a supported grid size (1) or not (0). Host only. */
 int pin_size_supported(int n);
 
-/* Device bytes pin_plan_create allocates for `desc` (workspace, tables); host only. */
+/* Device bytes pin_plan_create allocates for `desc` (workspace, tables); host only.  On small grids
+ * the collapse passes take several radii a launch and the workspace holds that many radii's slots
+ * (up to 256 MB); where that much memory is not free, pin_plan_create takes one radius's. */
 pin_status pin_plan_workspace_bytes(const pin_plan_desc* desc, size_t* bytes);
 
 /* Validate `desc` without touching the GPU. */
@@ -118,8 +120,9 @@ pin_status pin_collapse_reset(pin_plan plan, void* F, uint8_t* ridx, hipStream_t
 pin_status pin_collapse_times_range(pin_plan plan, const void* dk, void* F, uint8_t* ridx,
                                     int r_begin, int r_end, hipStream_t stream);
 
-/* pin_collapse_reset followed by pin_collapse_times_range over all radii: F_max and the index
- * of R_max (255 where no radius gives a positive F). */
+/* The result of pin_collapse_reset followed by pin_collapse_times_range over all radii: F_max and
+ * the index of R_max (255 where no radius gives a positive F).  The faster form: it reads no
+ * earlier state, so it takes the radii in the order that leaves most points unchanged. */
 pin_status pin_collapse_times(pin_plan plan, const void* dk, void* F, uint8_t* ridx,
                               hipStream_t stream);
 
@@ -253,7 +256,7 @@ pin_status pin_inverse_collapse_time(pin_plan plan, const void* T6, size_t count
 /* pin_collapse_times for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): no plan, no hipMalloc/hipFree,
  * no copy from host memory and no host wait -- only kernel launches on `stream`.  The workspace a
- * plan would allocate (11 half-spectrum slots, twiddle and window tables) is one static device
+ * plan would allocate (half-spectrum slots, twiddle and window tables) is one static device
  * array of 96 MiB that the library holds on each device it runs on until the process ends; its
  * device address is looked up once per device on the first call there, so make that first call
  * outside stream capture: later calls queue kernels only and can be captured into a HIP graph

@@ -37,14 +37,16 @@ pin_status pin_plan_workspace_bytes(const pin_plan_desc* desc, size_t* bytes) {
   return guarded([&] {
     validate_desc(desc);
     if (bytes == nullptr) fail(PIN_ERR_INVALID_ARG, "bytes is NULL");
-    *bytes = workspace_bytes(desc->n, desc->n_radii, desc->prec == PIN_FP64);
+    const bool fp64 = desc->prec == PIN_FP64;
+    *bytes = workspace_bytes(desc->n, desc->n_radii, fp64, collapse_batch(desc->n, desc->n_radii, fp64, false));
   });
 }
 
 pin_status pin_plan_create(const pin_plan_desc* desc, pin_plan* out) {
   return guarded([&] {
     if (out == nullptr) fail(PIN_ERR_INVALID_ARG, "out is NULL");
-    *out = plan_create(desc, desc ? desc->n_radii : 0);
+    validate_desc(desc);
+    *out = plan_create(desc, desc->n_radii, collapse_batch(desc->n, desc->n_radii, desc->prec == PIN_FP64, false));
   });
 }
 
@@ -91,7 +93,7 @@ pin_status pin_collapse_times_range(pin_plan plan, const void* dk, void* F, uint
       fail(PIN_ERR_INVALID_ARG, "radius range must satisfy 0 <= r_begin < r_end <= n_radii");
     check_device_range(dk, plan->half_spectrum_bytes(), "dk");
     check_field_outputs(plan, F, ridx);
-    plan_run_radii(plan, dk, F, ridx, r_begin, r_end, stream);
+    plan_run_radii(plan, dk, F, ridx, nullptr, r_begin, r_end, false, stream);
   });
 }
 
@@ -100,8 +102,7 @@ pin_status pin_collapse_times(pin_plan plan, const void* dk, void* F, uint8_t* r
     check_plan(plan);
     check_device_range(dk, plan->half_spectrum_bytes(), "dk");
     check_field_outputs(plan, F, ridx);
-    plan_reset(plan, F, ridx, stream);
-    plan_run_radii(plan, dk, F, ridx, 0, plan->nr, stream);
+    plan_run_radii(plan, dk, F, ridx, nullptr, 0, plan->nr, true, stream);
   });
 }
 
@@ -109,7 +110,8 @@ pin_status pin_plan_velocity_workspace_bytes(const pin_plan_desc* desc, size_t* 
   return guarded([&] {
     validate_desc(desc);
     if (bytes == nullptr) fail(PIN_ERR_INVALID_ARG, "bytes is NULL");
-    *bytes = velocity_workspace_bytes(desc->n, desc->prec == PIN_FP64);
+    const bool fp64 = desc->prec == PIN_FP64;
+    *bytes = velocity_workspace_bytes(desc->n, fp64, collapse_batch(desc->n, desc->n_radii, fp64, true));
   });
 }
 
@@ -131,7 +133,7 @@ pin_status pin_collapse_times_range_v(pin_plan plan, const void* dk, void* F, ui
     check_device_range(dk, plan->half_spectrum_bytes(), "dk");
     check_field_outputs(plan, F, ridx);
     check_device_range(vmax, 3 * plan->real_field_bytes(), "vmax");
-    plan_run_radii_v(plan, dk, F, ridx, vmax, r_begin, r_end, stream);
+    plan_run_radii(plan, dk, F, ridx, vmax, r_begin, r_end, false, stream);
   });
 }
 
@@ -141,8 +143,7 @@ pin_status pin_collapse_times_v(pin_plan plan, const void* dk, void* F, uint8_t*
     check_device_range(dk, plan->half_spectrum_bytes(), "dk");
     check_field_outputs(plan, F, ridx);
     check_device_range(vmax, 3 * plan->real_field_bytes(), "vmax");
-    plan_reset_v(plan, F, ridx, vmax, stream);
-    plan_run_radii_v(plan, dk, F, ridx, vmax, 0, plan->nr, stream);
+    plan_run_radii(plan, dk, F, ridx, vmax, 0, plan->nr, true, stream);
   });
 }
 

@@ -27,10 +27,11 @@ void prep(const void* dk, void* g0, double scale, hipStream_t s) {
                      static_cast<VV*>(g0), (RR)scale);
 }
 
-void xpass(int mode, const void* dk, void* out, const void* wtab, const void* tw, double scale, hipStream_t s) {
+void xpass(int mode, const void* dk, void* out, const void* wtab, const void* tw, double scale, int nb,
+           hipStream_t s) {
   using S = Strided<RR, NN, +1>;
   if (mode == 0) {
-    hipLaunchKernelGGL((k_xpass<RR, NN, 0>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(dk),
+    hipLaunchKernelGGL((k_xpass<RR, NN, 0>), dim3(S::GRID, nb), dim3(S::T), 0, s, static_cast<const VV*>(dk),
                        static_cast<VV*>(out), static_cast<const RR*>(wtab), static_cast<const VV*>(tw), (RR)scale);
   } else {
     hipLaunchKernelGGL((k_xpass<RR, NN, 1>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(dk),
@@ -55,10 +56,10 @@ void xpass_lpt3(const void* in, void* out, const void* tw, double scale, hipStre
                      static_cast<VV*>(out), static_cast<const VV*>(tw), (RR)scale);
 }
 
-void ypass(int recipe, const void* in, void* out, const void* tw, hipStream_t s) {
+void ypass(int recipe, const void* in, void* out, const void* tw, int nb, hipStream_t s) {
   if (recipe == 0) {
     using S = Strided<RR, NN, +1>;
-    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 0>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(in),
+    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 0>), dim3(S::GRID, nb), dim3(S::T), 0, s, static_cast<const VV*>(in),
                        static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
   } else if (recipe == 1) {
     using S = Strided<RR, NN, +1>;
@@ -80,36 +81,32 @@ void ypass(int recipe, const void* in, void* out, const void* tw, hipStream_t s)
 }
 
 // Hessian (3 packed slots to out) and v_max gradient (2 packed slots to gout) in one y pass.
-void ypass_hess_grad(const void* in, void* out, void* gout, const void* tw, hipStream_t s) {
+void ypass_hess_grad(const void* in, void* out, void* gout, const void* tw, int nb, hipStream_t s) {
   using S = Strided<RR, NN, +1>;
-  hipLaunchKernelGGL((k_ypass_packed<RR, NN, 5>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(in),
+  hipLaunchKernelGGL((k_ypass_packed<RR, NN, 5>), dim3(S::GRID, nb), dim3(S::T), 0, s, static_cast<const VV*>(in),
                      static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(gout));
 }
 
-void zpass_collapse(const void* in, const void* tw, void* F, uint8_t* ridx, int r, double sphere_gain, hipStream_t s) {
-  using Z = ZPass<RR, NN, 3, EPI_COLLAPSE>;
-  ZArgs a{};
-  a.F = F;
-  a.ridx = ridx;
-  a.r = r;
-  a.cc.sphere_gain = sphere_gain;
-  hipLaunchKernelGGL((k_zpass<RR, NN, 3, EPI_COLLAPSE>), dim3(Z::GRID), dim3(Z::T), 0, s,
-                     static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
+template <bool VEL, bool WHOLE> void zcollapse_launch(const CollapseStep& c, const ZCollapseArgs& a, hipStream_t s) {
+  using Z = ZCollapse<RR, NN, VEL, WHOLE>;
+  hipLaunchKernelGGL((k_zcollapse<RR, NN, VEL, WHOLE>), dim3(Z::GRID, c.groups), dim3(Z::T), 0, s,
+                     static_cast<const VV*>(c.in), static_cast<const VV*>(c.tw), a);
 }
 
-void zpass_collapse_v(const void* in, const void* gin, const void* tw, void* F, uint8_t* ridx, void* vmax, int r,
-                      double sphere_gain, double vscale, hipStream_t s) {
-  using Z = ZPass<RR, NN, 3, EPI_COLLAPSE_V>;
-  ZArgs a{};
-  a.F = F;
-  a.ridx = ridx;
-  a.r = r;
-  a.cc.sphere_gain = sphere_gain;
-  a.gin = gin;
-  a.vout = vmax;
-  a.vscale = vscale;
-  hipLaunchKernelGGL((k_zpass<RR, NN, 3, EPI_COLLAPSE_V>), dim3(Z::GRID), dim3(Z::T), 0, s,
-                     static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
+void zcollapse(const CollapseStep& c, hipStream_t s) {
+  constexpr size_t vol = (size_t)NN * NN * NN;
+  RR* Fg = static_cast<RR*>(c.groups > 1 ? c.part : c.F);
+  uint8_t* rg = c.groups > 1 ? reinterpret_cast<uint8_t*>(Fg + (size_t)c.groups * vol) : c.ridx;
+  ZCollapseArgs a{c.F, Fg, rg, c.r0, c.nb, c.fresh, CollapseConst{c.sphere_gain}, c.gin, c.vmax, c.vscale};
+  if (c.gin != nullptr)
+    c.whole ? zcollapse_launch<true, true>(c, a, s) : zcollapse_launch<true, false>(c, a, s);
+  else
+    c.whole ? zcollapse_launch<false, true>(c, a, s) : zcollapse_launch<false, false>(c, a, s);
+  if (c.groups > 1) {
+    const int block = 256;
+    hipLaunchKernelGGL((k_merge<RR>), dim3((unsigned)((vol + block - 1) / block)), dim3(block), 0, s, Fg, rg, c.groups,
+                       vol, static_cast<RR*>(c.F), c.ridx, c.whole, c.fresh);
+  }
 }
 
 void zpass_store(int nc, const void* in, const void* tw, void* out, hipStream_t s) {
@@ -194,11 +191,12 @@ void collapse_points(const void* t6, size_t count, void* F, double sphere_gain, 
 
 const SizeOps* PIN_CAT(ops_, PIN_INST_FP64, PIN_INST_N)() {
   static const SizeOps ops = {
-      NN, PIN_INST_FP64 != 0, prep, xpass, xpass_fwdinv, xpass_lpt3, ypass, ypass_hess_grad, zpass_collapse, zpass_collapse_v,
-      zpass_store, zpass_mu2, zpass_lpt3, grf, reset, redshift, zero, collapse_points,
+      NN, PIN_INST_FP64 != 0, prep, xpass, xpass_fwdinv, xpass_lpt3, ypass, ypass_hess_grad, zcollapse,
+      ZCollapse<RR, NN, false, true>::GRID * ZCollapse<RR, NN, false, true>::WAVES, BatchRule<RR, NN>::RADII,
+      BatchRule<RR, NN>::RADII_V, zpass_store, zpass_mu2, zpass_lpt3, grf, reset, redshift, zero, collapse_points,
       LaunchShape{Strided<RR, NN, +1>::GRID, Strided<RR, NN, +1>::T},
       LaunchShape{Strided<RR, NN, +1>::GRID, Strided<RR, NN, +1>::T},
-      LaunchShape{ZPass<RR, NN, 3, EPI_COLLAPSE>::GRID, ZPass<RR, NN, 3, EPI_COLLAPSE>::T}};
+      LaunchShape{ZCollapse<RR, NN, false, true>::GRID, ZCollapse<RR, NN, false, true>::T}};
   return &ops;
 }
 

@@ -162,6 +162,20 @@ template <typename V> __device__ __forceinline__ void st_stream(V* p, V v) {
   __builtin_nontemporal_store(w, reinterpret_cast<R2*>(p));
 }
 
+// Whether `count` half slots fit the last-level cache (256 MB), and how often.
+template <typename R, int N> constexpr int slots_fit(int count) {
+  return (int)(((size_t)256 << 20) / (count * (size_t)N * N * (N / 2) * 2 * sizeof(R)));
+}
+
+// Store into a slot between two passes: plain where one radius's slots (9 half slots, 13 with v_max)
+// fit the last-level cache and the next pass finds them there, streamed past the caches otherwise
+// (plain at 192^3 float32: x pass 34 -> 37 us, y pass 70 -> 62, z pass 54 -> 52; where the slots do
+// not fit streaming is the faster: 1.04 -> 1.01 ms for the 512^3 y pass, and at 192^3 float32 with
+// v_max, 368 MB, plain stores made the z pass 116 -> 138 us).
+template <typename R, int N, int SLOTS = 9, typename V> __device__ __forceinline__ void st_slot(V* p, V v) {
+  if constexpr (slots_fit<R, N>(SLOTS) > 0) *p = v; else st_stream(p, v);
+}
+
 // Streaming load, for the last read of a tile (its lines need not stay in L2).
 template <typename V> __device__ __forceinline__ V ld_stream(const V* p) {
   using R = decltype(p->x);
@@ -199,14 +213,15 @@ __global__ void k_prep(const typename Cplx<R>::type* __restrict__ dk, typename C
       out = V{d.x * m, d.y * m};
     }
   }
-  st_stream(&g0[PrepLayout<R, N>::index(x, y, z)], out);
+  st_slot<R, N>(&g0[PrepLayout<R, N>::index(x, y, z)], out);
 }
 
 // ---------------------------------------------------------------------------------------------
 // x pass.  MODE 0 (Hessian): input g0 (k_prep's tiled half slot), 3 outputs, multiplier
 // W(x)W(y)W(z) from the window row wtab (never null; a row of ones for no smoothing).  MODE 1
 // (gradient): input the user half spectrum, 2 outputs, multiplier i * scale / f^2 (wtab
-// unused).  Outputs: half slots.  Loads are unconditional (lanes without an element read an
+// unused).  Outputs: half slots.  blockIdx.y is the radius within a batch (MODE 0): its window row
+// follows the first one's, its three outputs the previous radius's.  Loads are unconditional (lanes without an element read an
 // in-bounds address and discard it): a load under a per-lane branch would make the compiler
 // wait for each one before issuing the next.
 template <typename R, int N, int MODE>
@@ -221,6 +236,10 @@ k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* _
   __shared__ V lds[E::LDS_ELEMS];
   __shared__ V s_tw[tw_elems(N)];
   const int t = threadIdx.x;
+  if constexpr (MODE == 0) {
+    wtab += (size_t)blockIdx.y * N;
+    out += (size_t)blockIdx.y * 3 * S::HSLOT;
+  }
   load_twiddles<N, S::T>(s_tw, tw, t);
   const int bt = xcd_tile(blockIdx.x, S::GRID);
   const int zt = bt % S::NZT;
@@ -254,7 +273,7 @@ k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* _
       // while the y pass runs (y pass 1.04 -> 1.01 ms at 512^3)
       if (ok) {
 #pragma unroll
-        for (int s = 0; s < E::R0; ++s) st_stream(out + a * S::HSLOT + ((size_t)(j + s * M) * N + y) * HZ + z, u[0][s]);
+        for (int s = 0; s < E::R0; ++s) st_slot<R, N>(out + a * S::HSLOT + ((size_t)(j + s * M) * N + y) * HZ + z, u[0][s]);
       }
     }
     return;
@@ -307,7 +326,7 @@ k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* _
       if (ok[k]) {
 #pragma unroll
         for (int s = 0; s < E::R0; ++s)
-          st_stream(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], u[k][s]);
+          st_slot<R, N>(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], u[k][s]);
       }
   }
 }
@@ -377,7 +396,7 @@ k_xpass_fwdinv(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
       if (ok[k]) {
 #pragma unroll
         for (int s = 0; s < E::R0; ++s)
-          st_stream(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], u[k][s]);
+          st_slot<R, N>(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], u[k][s]);
       }
   }
 }
@@ -455,7 +474,7 @@ k_xpass_lpt3(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::ty
       if (ok[k]) {
 #pragma unroll
         for (int s = 0; s < E::R0; ++s)
-          st_stream(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], v[a][k][s]);
+          st_slot<R, N>(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], v[a][k][s]);
       }
   }
 }
@@ -525,9 +544,14 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
   using E = typename S::E;
   constexpr int PS = S::PS, HZ = S::HZ, M = N / E::R0;
   constexpr size_t PSLOT = (size_t)N * N * N;
+  constexpr int SLOTS = RC::SPLIT > 0 ? 13 : 9;
   __shared__ V lds[E::LDS_ELEMS];
   __shared__ V s_tw[tw_elems(N)];
   const int t = threadIdx.x;
+  // blockIdx.y: the radius within a batch, its slots behind the previous radius's
+  in += (size_t)blockIdx.y * RC::NIN * S::HSLOT;
+  out += (size_t)blockIdx.y * (RC::SPLIT > 0 ? RC::SPLIT : RC::Q) * PSLOT;
+  if constexpr (RC::SPLIT > 0) out2 += (size_t)blockIdx.y * (RC::Q - RC::SPLIT) * PSLOT;
   load_twiddles<N, S::T>(s_tw, tw, t);
   const int bt = xcd_tile(blockIdx.x, S::GRID);
   const int zt = bt % S::NZT;
@@ -608,10 +632,10 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
             V* second =
                 reinterpret_cast<V*>(plane + (unsigned)L::index(0, jv[k] + s * M, zv[k] + HZ) * (unsigned)sizeof(V));
             if (sgn > 0) {
-              st_stream(first, u[k][s]);
-              if (!has_b && zv[k] > 0) st_stream(second, conj(u[k][s]));
+              st_slot<R, N, SLOTS>(first, u[k][s]);
+              if (!has_b && zv[k] > 0) st_slot<R, N, SLOTS>(second, conj(u[k][s]));
             } else if (zv[k] > 0) {
-              st_stream(second, conj(u[k][s]));
+              st_slot<R, N, SLOTS>(second, conj(u[k][s]));
             }
           }
         }
@@ -656,14 +680,14 @@ k_ypass_fwd(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::typ
   for (int k = 0; k < E::K0; ++k)
     if (ok[k]) {
 #pragma unroll
-      for (int s = 0; s < E::R0; ++s) st_stream(out + ((size_t)x * N + jj[k] + s * M) * HZ + zz[k], v[k][s]);
+      for (int s = 0; s < E::R0; ++s) st_slot<R, N>(out + ((size_t)x * N + jj[k] + s * M) * HZ + zz[k], v[k][s]);
     }
 }
 
 // ---------------------------------------------------------------------------------------------
 // z pass: inverse transform along z of Q packed slots (two real components each) and the
 // per-point epilogue.
-enum ZEpi { EPI_COLLAPSE = 0, EPI_STORE = 1, EPI_MU2 = 2, EPI_COLLAPSE_V = 3, EPI_LPT3 = 4 };
+enum ZEpi { EPI_STORE = 1, EPI_MU2 = 2, EPI_LPT3 = 4 };
 
 template <typename R, int N, int Q, int EPI>
 struct ZPass {
@@ -678,16 +702,53 @@ struct ZPass {
   static_assert(E::K0 == ZT::QL, "z pass: one butterfly per transform per thread");
 };
 
+// One thread's elements of packed z lines: n = j + s N/R0, s < R0, of line `line`.
+//
+// Packed storage of C[n]: P[n] for n < N/2, P[3N/2 - n] for n > N/2; R0 is even, so elements
+// s < R0/2 are the first kind and s >= R0/2 the second.  Loads are unconditional (the caller
+// passes a line in range); the Nyquist element n = N/2 (lane j = 0, s = R0/2) reads P[N/2], which
+// is never written, and is replaced by zero.  Offsets of element j + s M0, of the Nyquist slot and
+// of element 3N/2 - j - s M0 = (3N/2 - j) - s M0 are the same for every slot.  A workgroup's lines
+// share one x-plane when P divides N: the plane's base is then uniform and the offsets within it
+// (bytes) fit 32 bits, so each load adds one 32-bit offset to a scalar base.
+template <typename R, int N, int P> struct ZLoader {
+  using V = typename Cplx<R>::type;
+  using L = PackedLayout<R, N>;
+  static constexpr int R0 = factorize(N).r[0];
+  static constexpr int M0 = N / R0, HZ = N / 2;
+  static constexpr bool PLANE = N % P == 0;
+  static constexpr unsigned STEPB = (unsigned)(L::STEP * sizeof(V));
+  static_assert(R0 % 2 == 0 && M0 * (R0 / 2) == HZ, "z pass: the first half of the elements is n < N/2");
+  static_assert((size_t)3 * N * N * sizeof(V) < ((size_t)1 << 32), "z pass: plane offsets must fit 32 bits");
+  size_t plane;
+  unsigned o_lo, o_ny, o_hi;
+  bool ny;
+
+  __device__ __forceinline__ ZLoader(int line, int j) {
+    const int ly = line % N;
+    const int lx = PLANE ? (int)(blockIdx.x * P / N) : line / N;
+    plane = (size_t)lx * N * N;
+    o_lo = (unsigned)L::index(0, ly, j) * (unsigned)sizeof(V);
+    o_ny = (unsigned)L::index(0, ly, j == 0 ? HZ : N - j) * (unsigned)sizeof(V);
+    o_hi = (unsigned)L::index(0, ly, 3 * HZ - j) * (unsigned)sizeof(V);
+    ny = j == 0;
+  }
+  __device__ __forceinline__ void load(const V* slot, V (&dst)[R0]) const {
+    const char* base = reinterpret_cast<const char*>(slot + plane);
+#pragma unroll
+    for (int s = 0; s < R0 / 2; ++s) dst[s] = *reinterpret_cast<const V*>(base + (o_lo + s * STEPB));
+    {
+      const V x = *reinterpret_cast<const V*>(base + o_ny);
+      dst[R0 / 2] = ny ? V{R(0), R(0)} : x;
+    }
+#pragma unroll
+    for (int s = R0 / 2 + 1; s < R0; ++s) dst[s] = *reinterpret_cast<const V*>(base + (o_hi - s * STEPB));
+  }
+};
+
 struct ZArgs {
-  void* F;          // EPI_COLLAPSE: running F_max (R)
-  uint8_t* ridx;    // EPI_COLLAPSE: running radius index
-  int r;            // EPI_COLLAPSE: radius index of this launch
   int nc;           // EPI_STORE: number of real components to store (<= 2Q)
   void* out;        // EPI_STORE: [nc][N^3] real; EPI_MU2: one half slot (complex)
-  CollapseConst cc;
-  const void* gin;  // EPI_COLLAPSE_V: the two packed gradient slots (y-pass recipe 3)
-  void* vout;       // EPI_COLLAPSE_V: v_max [3][N^3] (R)
-  double vscale;    // EPI_COLLAPSE_V: L / 2 pi
   void* t6;         // EPI_MU2: when not null, the six components are stored to t6[6][N^3] (R);
                     // EPI_LPT3: the first-order tensor T1 [6][N^3] read at each point
 };
@@ -727,48 +788,10 @@ k_zpass(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R>::t
   const int line = blockIdx.x * P + p;
   const bool line_ok = Z::LINES % P == 0 || line < Z::LINES;
   V v[Q][R0];
-  // collapse epilogue: the running maximum of this thread's points, fetched with the inputs so
-  // that its latency hides behind the transforms
-  R fold[R0];
-  if constexpr (EPI == EPI_COLLAPSE || EPI == EPI_COLLAPSE_V) {
-    const R* F = static_cast<const R*>(args.F);
-#pragma unroll
-    for (int s = 0; s < R0; ++s) fold[s] = F[(size_t)(line_ok ? line : Z::LINES - 1) * N + j + s * M0];
-  }
-  // Packed storage of C[n]: P[n] for n < N/2, P[3N/2 - n] for n > N/2; R0 is even, so elements
-  // s < R0/2 are the first kind and s >= R0/2 the second.  Loads are unconditional (a wave past
-  // the last line reads the last line and stores nothing); the Nyquist element n = N/2 (lane
-  // j = 0, s = R0/2) reads P[N/2], which is never written, and is replaced by zero.
-  static_assert(R0 % 2 == 0 && M0 * (R0 / 2) == HZ, "z pass: the first half of the elements is n < N/2");
   const int lineL = line_ok ? line : Z::LINES - 1;
-  using L = PackedLayout<R, N>;
-  static_assert(L::M0 == M0, "z pass: the packed layout's element stride");
-  // Offsets of element j + s M0, of the Nyquist slot and of element 3N/2 - j - s M0 =
-  // (3N/2 - j) - s M0, the same for every slot.  The workgroup's lines share one x-plane when P
-  // divides N: the plane's base is then uniform and the offsets within it (bytes) fit 32 bits,
-  // so each load adds one 32-bit offset to a scalar base.
-  const int ly = lineL % N;
-  constexpr bool PLANE = N % P == 0;
-  const int lx = PLANE ? (int)(blockIdx.x * P / N) : lineL / N;
-  const size_t plane = (size_t)lx * N * N;
-  const unsigned o_lo = (unsigned)L::index(0, ly, j) * (unsigned)sizeof(V);
-  const unsigned o_ny = (unsigned)L::index(0, ly, j == 0 ? HZ : N - j) * (unsigned)sizeof(V);
-  const unsigned o_hi = (unsigned)L::index(0, ly, 3 * HZ - j) * (unsigned)sizeof(V);
-  constexpr unsigned STEPB = (unsigned)(L::STEP * sizeof(V));
-  static_assert((size_t)3 * N * N * sizeof(V) < ((size_t)1 << 32), "z pass: plane offsets must fit 32 bits");
-  auto load_line = [&](const V* slot, V(&dst)[R0]) {
-    const char* base = reinterpret_cast<const char*>(slot + plane);
+  const ZLoader<R, N, P> ld(lineL, j);
 #pragma unroll
-    for (int s = 0; s < R0 / 2; ++s) dst[s] = *reinterpret_cast<const V*>(base + (o_lo + s * STEPB));
-    {
-      const V x = *reinterpret_cast<const V*>(base + o_ny);
-      dst[R0 / 2] = j == 0 ? V{R(0), R(0)} : x;
-    }
-#pragma unroll
-    for (int s = R0 / 2 + 1; s < R0; ++s) dst[s] = *reinterpret_cast<const V*>(base + (o_hi - s * STEPB));
-  };
-#pragma unroll
-  for (int q = 0; q < Q; ++q) load_line(in + (size_t)q * PSLOT, v[q]);
+  for (int q = 0; q < Q; ++q) ld.load(in + (size_t)q * PSLOT, v[q]);
   if constexpr (Z::ZT::QL == Q) {
     E::run(v, lds, s_tw, t);
   } else {
@@ -785,50 +808,7 @@ k_zpass(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R>::t
       return c == 0 ? v[0][s].x : c == 1 ? v[0][s].y : v[1][s].x;
     }
   };
-  if constexpr (EPI == EPI_COLLAPSE || EPI == EPI_COLLAPSE_V) {
-    static_assert(Q == 3, "collapse needs the six components");
-    R* F = static_cast<R*>(args.F);
-    bool upd[R0];
-#pragma unroll
-    for (int s = 0; s < R0; ++s) {
-      const size_t idx = (size_t)line * N + j + s * M0;
-      R fr;
-      if constexpr (sizeof(R) == 4) {
-        fr = collapse_point_mixed(comp(0, s), comp(1, s), comp(2, s), comp(3, s), comp(4, s), comp(5, s),
-                                  (float)args.cc.sphere_gain);
-      } else {
-        fr = (R)collapse_point(comp(0, s), comp(1, s), comp(2, s), comp(3, s), comp(4, s), comp(5, s), args.cc);
-      }
-      upd[s] = line_ok && fr > fold[s];
-      if (upd[s]) {
-        // streamed: read again only at the next radius, after the x and y passes
-        __builtin_nontemporal_store(fr, &F[idx]);
-        __builtin_nontemporal_store((uint8_t)args.r, &args.ridx[idx]);
-      }
-    }
-    if constexpr (EPI == EPI_COLLAPSE_V) {
-      // v_max: the smoothed gradient at this radius, transformed only now (the Hessian data is
-      // dead) and stored where F_max grew
-      const V* gin = static_cast<const V*>(args.gin);
-      V g[2][R0];
-      load_line(gin, g[0]);
-      load_line(gin + PSLOT, g[1]);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) E::run(*reinterpret_cast<V(*)[1][R0]>(&g[q]), lds, s_tw, t);
-      R* vout = static_cast<R*>(args.vout);
-      constexpr size_t VOL = (size_t)N * N * N;
-      const R vs = (R)args.vscale;
-#pragma unroll
-      for (int s = 0; s < R0; ++s) {
-        if (upd[s]) {
-          const size_t idx = (size_t)line * N + j + s * M0;
-          __builtin_nontemporal_store(g[0][s].x * vs, &vout[idx]);
-          __builtin_nontemporal_store(g[0][s].y * vs, &vout[VOL + idx]);
-          __builtin_nontemporal_store(g[1][s].x * vs, &vout[2 * VOL + idx]);
-        }
-      }
-    }
-  } else if constexpr (EPI == EPI_STORE) {
+  if constexpr (EPI == EPI_STORE) {
     R* out = static_cast<R*>(args.out);
     constexpr size_t VOL = (size_t)N * N * N;
     if (line_ok) {
@@ -936,9 +916,281 @@ k_zpass(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R>::t
       const V a = V{R(0.5) * (zk.x + zn.x), R(0.5) * (zk.y - zn.y)};   // (Z_k + conj Z_{N-k})/2
       const V b = V{R(0.5) * (zk.y + zn.y), R(0.5) * (zn.x - zk.x)};   // (Z_k - conj Z_{N-k})/(2i)
       const int l0 = blockIdx.x * P + 2 * u;
-      if (l0 < Z::LINES) st_stream(out + (size_t)l0 * HZ + k, a);
-      if (l0 + 1 < Z::LINES) st_stream(out + (size_t)(l0 + 1) * HZ + k, b);
+      if (l0 < Z::LINES) st_slot<R, N>(out + (size_t)l0 * HZ + k, a);
+      if (l0 + 1 < Z::LINES) st_slot<R, N>(out + (size_t)(l0 + 1) * HZ + k, b);
     }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// z pass with the collapse epilogue: inverse transforms along z of the three packed slots of each
+// radius of a batch, the collapse model per point, and the running maximum over the radii.
+//
+// Order of the radii.  A whole call (WHOLE) takes the radii from the last (the smallest) to the
+// first: F grows towards small radii at most points, so the maximum is nearly final after a few
+// radii and few points change later (5.8% of the points per radius against 67% in increasing
+// index, counted over 40 radii on a 2 Mpc/h grid).  Ties then go to the radius taken last, which is
+// the smaller index, as in increasing order, where they go to the first.  A range call has to be
+// the next part of a walk in increasing order, whatever its state holds, and takes its radii so.
+//
+// Points that cannot change are left out of a whole call.  For every symmetric tensor T,
+// F(T) > 0 implies
+//     F <= delta / 2 + 0.6915 |T|,   delta = tr T, |T| = sqrt(sum T_ij^2)
+// (both sides scale with T; the constant is the largest value of (F - delta/2)/|T| over all
+// eigenvalue directions, sampled at a million points of the ordered ones), so a point whose
+// running maximum f has f - delta/2 > 0.7 |T| keeps it: the 1.2% of slack covers the float32
+// rounding of T's norm and of F.  21% of the points are left for the model (counted as above), too
+// spread out for whole waves to skip it (68% of the 64-point rows hold one), so each wave gathers
+// those of its points in LDS and evaluates them densely, 64 at a time.
+struct ZCollapseArgs {
+  const void* F;       // running F_max (R) before this batch
+  void* Fout;          // F_max after it; with groups, [groups][N^3]
+  uint8_t* ridx;       // radius index of F_max; with groups, [groups][N^3]
+  int r0;              // radius index of the batch's first slots
+  int nb;              // radii in the batch
+  bool fresh;          // no state before this batch: F, ridx (v_max) are written at every point
+  CollapseConst cc;
+  const void* gin;     // v_max: the packed gradient slots (y-pass recipe 5), two per radius
+  void* vout;          // v_max [3][N^3] (R)
+  double vscale;       // v_max: L / 2 pi
+};
+
+template <typename R> __device__ __forceinline__ R collapse_of(R xx, R xy, R xz, R yy, R yz, R zz, const CollapseConst& cc) {
+  if constexpr (sizeof(R) == 4) {
+    return collapse_point_mixed(xx, xy, xz, yy, yz, zz, (float)cc.sphere_gain);
+  } else {
+    return collapse_point(xx, xy, xz, yy, yz, zz, cc);
+  }
+}
+
+// Whether a point with tensor T could reach the running maximum f.  The term added to |T|^2 keeps
+// tensors whose squares underflow; a NaN or an overflow keeps its point.
+template <typename R> __device__ __forceinline__ bool may_reach(R xx, R xy, R xz, R yy, R yz, R zz, R f) {
+  const R off = xy * xy + xz * xz + yz * yz;
+  const R norm2 = (sizeof(R) == 4 ? R(1e-30) : R(1e-200)) + R(0.49) * (xx * xx + yy * yy + zz * zz + R(2) * off);
+  const R h = f - R(0.5) * (xx + yy + zz);
+  return !(h > R(0) && h * h > norm2);
+}
+
+// Place of this lane among the lanes of mask m, counted from first.
+__device__ __forceinline__ unsigned lane_rank(unsigned long long m, unsigned first) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, first));
+}
+
+// Radii that share a launch of the collapse passes.  The launches of a small grid are short (at
+// 64^3 a pass over one radius took 8-9 us, of which its data needs 1-2), so as many radii share one
+// as keep the slots between the passes, 9 half slots a radius, within the last-level cache.  At
+// 128^3 float32, 32 radii: 2 radii a launch 1.40 ms, 3 (this rule) 1.32, 4 1.43; 96^3 float64, 24
+// radii: 2 a launch 1.42 ms, 4 (this rule) 1.24, 5 1.25.
+template <typename R, int N> struct BatchRule {
+  static constexpr int most(int fit) { return fit < 1 ? 1 : fit < 16 ? fit : 16; }
+  static constexpr int RADII = most(slots_fit<R, N>(9));
+  static constexpr int RADII_V = most(slots_fit<R, N>(13));   // with v_max: 4 half slots more
+  static constexpr bool MANY = RADII > 1;
+};
+
+// Points of one wave gathered at a time: half of its 64 R0.
+template <int R0> constexpr int kGather = 32 * R0;
+
+template <typename R, int N, bool VEL, bool WHOLE>
+struct ZCollapse {
+  using V = typename Cplx<R>::type;
+  using ZT = ZTile<R, N, 3>;
+  static constexpr int P = ZT::P;
+  static constexpr int T = ZT::T;
+  using E = Engine<V, N, P, 1, false, T, +1>;
+  static constexpr int LINES = N * N;
+  static constexpr int GRID = (LINES + P - 1) / P;
+  static constexpr int WAVES = (T + 63) / 64;
+  static constexpr int GATHER = kGather<E::R0>;
+  static constexpr size_t GATHER_BYTES = WHOLE ? (size_t)WAVES * GATHER * 6 * sizeof(R) : 0;
+  static constexpr size_t LDS_BYTES = E::LDS_ELEMS * sizeof(V) > GATHER_BYTES ? E::LDS_ELEMS * sizeof(V) : GATHER_BYTES;
+  static_assert(E::K0 == 1 && ZT::QL == 1, "z pass: one butterfly per transform per thread");
+  static constexpr int WPE = sizeof(R) == 8 ? (VEL ? 1 : 2) : (VEL || E::max_held() > 8 ? 3 : 4);
+};
+
+template <typename R, int N, bool VEL, bool WHOLE>
+__global__ void __launch_bounds__((ZCollapse<R, N, VEL, WHOLE>::T))
+__attribute__((amdgpu_waves_per_eu(ZCollapse<R, N, VEL, WHOLE>::WPE)))
+k_zcollapse(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R>::type* __restrict__ tw,
+            ZCollapseArgs args) {
+  using Z = ZCollapse<R, N, VEL, WHOLE>;
+  using V = typename Z::V;
+  using E = typename Z::E;
+  constexpr int P = Z::P, R0 = E::R0, M0 = N / R0;
+  constexpr size_t VOL = (size_t)N * N * N, PSLOT = VOL;
+  constexpr bool MANY = BatchRule<R, N>::MANY;   // one radius a launch otherwise
+  __shared__ __align__(16) unsigned char lds_bytes[Z::LDS_BYTES];
+  __shared__ V s_tw[tw_elems(N)];
+  V* lds = reinterpret_cast<V*>(lds_bytes);
+  const int t = threadIdx.x;
+  load_twiddles<N, Z::T>(s_tw, tw, t);
+  const int line = blockIdx.x * P + t / M0;
+  const bool line_ok = Z::LINES % P == 0 || line < Z::LINES;
+  const int lineL = line_ok ? line : Z::LINES - 1;
+  // this group's radii of the batch, every groups-th from its own (one group: all of them), and
+  // its outputs
+  const int groups = gridDim.y, g = blockIdx.y;
+  const int turns = (args.nb - g + groups - 1) / groups;
+  const bool dense = args.fresh || groups > 1;   // every point is written
+  R* F = static_cast<R*>(args.Fout) + (size_t)g * VOL;
+  uint8_t* ridx = args.ridx + (size_t)g * VOL;
+  const size_t at = (size_t)lineL * N + t % M0;
+  R* q = reinterpret_cast<R*>(lds_bytes) + (size_t)(t >> 6) * (Z::GATHER * 6);
+  // the running maximum of this thread's points: in registers, or in LDS where several radii share
+  // the launch (held across the transforms of a radius it would spill)
+  R fold[MANY ? 1 : R0];
+  __shared__ R s_fold[MANY ? R0 * Z::T : 1];
+  auto best = [&](int s) -> R& { return MANY ? s_fold[s * Z::T + t] : fold[MANY ? 0 : s]; };
+  // several radii a launch: index of the one that set fold, a byte per point, 255: none; stored
+  // at the end.  One radius: stored as it comes.  Streamed: read again only after other passes.
+  uint32_t rset[(R0 + 3) / 4];
+#pragma unroll
+  for (int s = 0; s < R0; ++s) best(s) = args.fresh ? R(0) : static_cast<const R*>(args.F)[at + s * M0];
+#pragma unroll
+  for (int s = 0; s < (R0 + 3) / 4; ++s) rset[s] = ~0u;
+#pragma unroll 1
+  for (int i = 0; i < (MANY ? turns : 1); ++i) {
+    const int b = WHOLE ? args.nb - 1 - g - i * groups : g + i * groups;
+    // an opaque copy: every address made from it would otherwise be computed ahead of the loop and
+    // held across the epilogue (33 spilled registers at 512^3)
+    int tt = t;
+    if constexpr (MANY) asm volatile("" : "+v"(tt));
+    const ZLoader<R, N, P> ld(line_ok ? blockIdx.x * P + tt / M0 : Z::LINES - 1, tt % M0);
+    V v[3][R0];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) ld.load(in + (size_t)(3 * b + c) * PSLOT, v[c]);
+    if (i > 0) __syncthreads();   // the gathered points of the radius before are read
+#pragma unroll
+    for (int c = 0; c < 3; ++c) E::run(*reinterpret_cast<V(*)[1][R0]>(&v[c]), lds, s_tw, tt);
+    // v[c][s] = (packed component 2c) + i (packed component 2c + 1): xy xz | yy yz | xx zz
+    bool upd[R0];
+    auto take = [&](int s, R fr) {
+      const R f = best(s);
+      upd[s] = line_ok && (fr > f || (WHOLE && fr == f && fr > R(0)));
+      if constexpr (MANY) {
+        if (upd[s]) best(s) = fr;
+        const uint32_t set = (rset[s / 4] & ~(0xFFu << (8 * (s % 4)))) | ((uint32_t)(args.r0 + b) << (8 * (s % 4)));
+        rset[s / 4] = upd[s] ? set : rset[s / 4];
+      } else if (upd[s] || (dense && line_ok)) {
+        __builtin_nontemporal_store(upd[s] ? fr : R(0), &F[at + s * M0]);
+        __builtin_nontemporal_store(upd[s] ? (uint8_t)args.r0 : (uint8_t)255, &ridx[at + s * M0]);
+      }
+    };
+    if constexpr (WHOLE) {
+      const unsigned long long me = 1ull << (t & 63);
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        constexpr int H = R0 / 2;
+        unsigned long long left[H];   // the lanes whose point is left for the model
+        unsigned total = 0;
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          const int s = half * H + h;
+          const bool need = line_ok && may_reach(v[2][s].x, v[0][s].x, v[0][s].y, v[1][s].x, v[1][s].y, v[2][s].y, best(s));
+          left[h] = __ballot(need);
+          if (need) {
+            R* e = q + lane_rank(left[h], total);
+            e[0] = v[2][s].x;
+            e[Z::GATHER] = v[0][s].x;
+            e[2 * Z::GATHER] = v[0][s].y;
+            e[3 * Z::GATHER] = v[1][s].x;
+            e[4 * Z::GATHER] = v[1][s].y;
+            e[5 * Z::GATHER] = v[2][s].y;
+          }
+          total += (unsigned)__popcll(left[h]);
+        }
+        // one wave's own part of LDS: its lanes run in step, so only the compiler has to be held
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (unsigned k = t & 63; k < total; k += 64) {
+          R* e = q + k;
+          e[0] = collapse_of<R>(e[0], e[Z::GATHER], e[2 * Z::GATHER], e[3 * Z::GATHER], e[4 * Z::GATHER],
+                                e[5 * Z::GATHER], args.cc);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        total = 0;
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          unsigned long long m = left[h];
+          asm volatile("" : "+s"(m));   // ranked again: kept from above, the ranks would hold H registers
+          R fr = R(0);                  // a point left out changes nothing
+          if (m & me) fr = q[lane_rank(m, total)];
+          take(half * H + h, fr);
+          total += (unsigned)__popcll(m);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < R0; ++s)
+        take(s, collapse_of<R>(v[2][s].x, v[0][s].x, v[0][s].y, v[1][s].x, v[1][s].y, v[2][s].y, args.cc));
+    }
+    if constexpr (VEL) {
+      // v_max: the smoothed gradient at this radius, transformed only now (the Hessian data is
+      // dead); in a whole call only where a line of this workgroup has a point that changed
+      R* vout = static_cast<R*>(args.vout);
+      const bool all = args.fresh && i == 0;
+      bool any = !WHOLE || all;
+#pragma unroll
+      for (int s = 0; s < R0; ++s) any = any || upd[s];
+      if (!WHOLE || __syncthreads_or(any)) {
+        const V* gin = static_cast<const V*>(args.gin) + (size_t)2 * b * PSLOT;
+        V w[2][R0];
+        ld.load(gin, w[0]);
+        ld.load(gin + PSLOT, w[1]);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) E::run(*reinterpret_cast<V(*)[1][R0]>(&w[c]), lds, s_tw, tt);
+        const R vs = (R)args.vscale;
+#pragma unroll
+        for (int s = 0; s < R0; ++s) {
+          if (upd[s] || (all && line_ok)) {
+            __builtin_nontemporal_store(upd[s] ? w[0][s].x * vs : R(0), &vout[at + s * M0]);
+            __builtin_nontemporal_store(upd[s] ? w[0][s].y * vs : R(0), &vout[VOL + at + s * M0]);
+            __builtin_nontemporal_store(upd[s] ? w[1][s].x * vs : R(0), &vout[2 * VOL + at + s * M0]);
+          }
+        }
+      }
+    }
+  }
+  if constexpr (MANY) {
+#pragma unroll
+    for (int s = 0; s < R0; ++s) {
+      const uint8_t r = (uint8_t)(rset[s / 4] >> (8 * (s % 4)));
+      if (line_ok && (r != 255 || dense)) {
+        __builtin_nontemporal_store(best(s), &F[at + s * M0]);
+        __builtin_nontemporal_store(r, &ridx[at + s * M0]);
+      }
+    }
+  }
+}
+
+// Groups' results [groups][VOL] into the running state: the largest F, of equal ones the smallest
+// radius index.  The state before the batch holds larger indices in a whole call and smaller ones
+// otherwise.
+template <typename R>
+__global__ void k_merge(const R* __restrict__ Fg, const uint8_t* __restrict__ rg, int groups, size_t vol, R* __restrict__ F,
+                        uint8_t* __restrict__ ridx, bool whole, bool fresh) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= vol) return;
+  R f = fresh ? R(0) : F[i];
+  const int before = whole ? 256 : -1;
+  int r = before;
+  for (int k = 0; k < groups; ++k) {
+    const size_t e = (size_t)k * vol + i;
+    const R fk = Fg[e];
+    const int rk = rg[e];   // 255: this group left the state as it was
+    if (rk != 255 && (fk > f || (fk == f && rk < r))) {
+      f = fk;
+      r = rk;
+    }
+  }
+  if (r != before || fresh) {
+    F[i] = f;
+    ridx[i] = (uint8_t)(r != before ? r : 255);
   }
 }
 

@@ -103,7 +103,7 @@ extern "C" pin_status pin_collapse_times_noalloc(const pin_plan_desc* desc, cons
   return guarded([&] {
     validate_desc(desc);
     const bool fp64 = desc->prec == PIN_FP64;
-    const size_t need = workspace_bytes(desc->n, desc->n_radii, fp64);
+    const size_t need = workspace_bytes(desc->n, desc->n_radii, fp64, 1);
     if (desc->n > kMaxN || need > kScratchBytes)
       fail(PIN_ERR_UNSUPPORTED_SIZE, "pin_collapse_times_noalloc: N=" + std::to_string(desc->n) + " with " +
                                          std::to_string(desc->n_radii) + " radii needs " + std::to_string(need) +
@@ -127,17 +127,20 @@ extern "C" pin_status pin_collapse_times_noalloc(const pin_plan_desc* desc, cons
     check_device_range(F, p.real_field_bytes(), "F");
     check_device_range(ridx, (size_t)p.n * p.n * p.n, "ridx");
 
+    // as many radii a launch as a plan's, or as the scratch array holds
+    p.batch = collapse_batch(p.n, p.nr, fp64, false);
+    while (p.batch > 1 && workspace_bytes(p.n, p.nr, fp64, p.batch) > kScratchBytes) --p.batch;
+    const size_t xs = p.batch > 1 ? 3 * (size_t)p.batch : 4;
     char* base = static_cast<char*>(scratch_address(dev));
     p.G = base;
     p.X = base + p.slot_bytes;
-    p.Y = base + 5 * p.slot_bytes;
-    p.tw = base + 11 * p.slot_bytes;
+    p.Y = base + (1 + xs) * p.slot_bytes;
+    p.tw = base + (1 + xs + 6 * (size_t)p.batch) * p.slot_bytes;
     p.wtab = static_cast<char*>(p.tw) + (size_t)p.n * p.complex_bytes();
     if (fp64)
       write_tables<double>(p.tw, p.wtab, desc, stream);
     else
       write_tables<float>(p.tw, p.wtab, desc, stream);
-    plan_reset(&p, F, ridx, stream);
-    plan_run_radii(&p, dk, F, ridx, 0, p.nr, stream);
+    plan_run_radii(&p, dk, F, ridx, nullptr, 0, p.nr, true, stream);
   });
 }

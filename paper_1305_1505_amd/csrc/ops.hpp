@@ -13,14 +13,31 @@ struct LaunchShape {
   int block;
 };
 
+// One batch of the collapse z pass.
+struct CollapseStep {
+  const void* in;     // 3 packed slots per radius
+  const void* gin;    // 2 packed gradient slots per radius, or null (no v_max)
+  const void* tw;
+  void* F;
+  uint8_t* ridx;
+  void* vmax;
+  void* part;         // groups > 1: groups * N^3 reals and as many bytes of scratch
+  int r0, nb;         // first radius index, radii
+  int groups;         // workgroups along the radii (1 with v_max)
+  bool whole;         // part of a call over all radii, taken from the last to the first
+  bool fresh;         // no state before this batch
+  double sphere_gain, vscale;
+};
+
 struct SizeOps {
   int n;
   bool fp64;
   // radius-independent Hessian input g0 = M dk scale / f^2 into one aligned slot
   void (*prep)(const void* dk, void* g0, double scale, hipStream_t s);
-  // x pass.  mode 0: Hessian from g0 (3 outputs, window table or null); mode 1: gradient from the
-  // user half spectrum (2 outputs).  out = first workspace slot of the outputs.
-  void (*xpass)(int mode, const void* dk, void* out, const void* wtab, const void* tw, double scale,
+  // x pass.  mode 0: Hessian from g0 (3 outputs per radius, nb radii with consecutive window rows
+  // from wtab); mode 1: gradient from the user half spectrum (2 outputs).  out = first workspace
+  // slot of the outputs.
+  void (*xpass)(int mode, const void* dk, void* out, const void* wtab, const void* tw, double scale, int nb,
                 hipStream_t s);
   // fused forward-x / inverse-x of a second-order source: one input slot -> two output slots
   // (gradient, 2LPT) or three (hess: the Hessian x-pass outputs)
@@ -29,17 +46,16 @@ struct SizeOps {
   void (*xpass_lpt3)(const void* in, void* out, const void* tw, double scale, hipStream_t s);
   // y pass: recipe 0 Hessian (3 half slots -> 3 packed slots), 1 gradient (2 half -> 2 packed),
   // 2 forward (1 half -> 1 half), 3 gradient times i from the Hessian x pass (2 half -> 2 packed),
-  // 4 three finished components (3 half -> 2 packed)
-  void (*ypass)(int recipe, const void* in, void* out, const void* tw, hipStream_t s);
+  // 4 three finished components (3 half -> 2 packed); nb radii (recipes 0 and 1), one otherwise
+  void (*ypass)(int recipe, const void* in, void* out, const void* tw, int nb, hipStream_t s);
   // Hessian y pass that also writes the v_max gradient (y recipe 3's slots) to gout
-  void (*ypass_hess_grad)(const void* in, void* out, void* gout, const void* tw, hipStream_t s);
-  // z pass (packed slots in) with the collapse epilogue at radius index r
-  void (*zpass_collapse)(const void* in, const void* tw, void* F, uint8_t* ridx, int r, double sphere_gain,
-                         hipStream_t s);
-  // z pass with the collapse epilogue and v_max: Hessian packed slots `in`, gradient packed
-  // slots `gin`; v_max [3][N^3] written where F_max grows, times vscale
-  void (*zpass_collapse_v)(const void* in, const void* gin, const void* tw, void* F, uint8_t* ridx, void* vmax,
-                           int r, double sphere_gain, double vscale, hipStream_t s);
+  void (*ypass_hess_grad)(const void* in, void* out, void* gout, const void* tw, int nb, hipStream_t s);
+  // z pass (packed slots in) with the collapse epilogue over a batch of radii, and v_max if gin is
+  // not null; with several groups, `part` takes each group's result and a second launch merges them
+  void (*zcollapse)(const CollapseStep& c, hipStream_t s);
+  // waves of one group of that pass; most radii one launch of the collapse passes takes, without
+  // and with v_max
+  int zwaves, batch, batch_v;
   // z pass storing nc = 6 (Hessian) or 3 (gradient) real components to out[nc][N^3]
   void (*zpass_store)(int nc, const void* in, const void* tw, void* out, hipStream_t s);
   // z pass computing the 2LPT source and its forward transform along z into one slot; the six

@@ -95,11 +95,19 @@ void validate_desc(const pin_plan_desc* d) {
   if (d->prec != PIN_FP32 && d->prec != PIN_FP64) fail(PIN_ERR_INVALID_ARG, "prec must be PIN_FP32 or PIN_FP64");
 }
 
-size_t workspace_bytes(int n, int n_radii, bool fp64) {
+int collapse_batch(int n, int n_radii, bool fp64, bool vel) {
+  const SizeOps* ops = find_ops(n, fp64);
+  const int b = vel ? ops->batch_v : ops->batch;
+  return b < n_radii ? b : n_radii;
+}
+
+static size_t xslots(int batch) { return batch > 1 ? 3 * (size_t)batch : 4; }
+
+size_t workspace_bytes(int n, int n_radii, bool fp64, int batch) {
   const size_t rb = fp64 ? 8 : 4;
   const size_t slot = (size_t)n * n * (n / 2) * 2 * rb;
   // workspace slots, twiddles, one window row per radius plus a row of ones (no smoothing)
-  return 11 * slot + (size_t)n * 2 * rb + (size_t)n * (n_radii + 1) * rb;
+  return (1 + xslots(batch) + 6 * (size_t)batch) * slot + (size_t)n * 2 * rb + (size_t)n * (n_radii + 1) * rb;
 }
 
 void check_device_range(const void* p, size_t bytes, const char* name) {
@@ -139,7 +147,7 @@ static const double* amp_table(pin_plan p) {
   return static_cast<const double*>(d);
 }
 
-pin_plan plan_create(const pin_plan_desc* desc, int radii_capacity) {
+pin_plan plan_create(const pin_plan_desc* desc, int radii_capacity, int batch) {
   validate_desc(desc);
   if (radii_capacity < desc->n_radii) radii_capacity = desc->n_radii;
   pin_plan p = new pin_plan_s();
@@ -160,8 +168,18 @@ pin_plan plan_create(const pin_plan_desc* desc, int radii_capacity) {
     p->slot_bytes = (size_t)p->n * p->n * (p->n / 2) * p->complex_bytes();
     p->tw = device_alloc((size_t)p->n * p->complex_bytes(), "twiddles");
     p->wtab = device_alloc((size_t)p->n * (p->nr_capacity + 1) * p->real_bytes, "windows");
-    p->X = device_alloc(4 * p->slot_bytes, "workspace X");
-    p->Y = device_alloc(6 * p->slot_bytes, "workspace Y");
+    p->batch = batch;
+    if (batch > 1 && (hipMalloc(&p->X, xslots(batch) * p->slot_bytes) != hipSuccess ||
+                      hipMalloc(&p->Y, 6 * batch * p->slot_bytes) != hipSuccess)) {
+      (void)hipGetLastError();
+      if (p->X) (void)hipFree(p->X);
+      p->X = p->Y = nullptr;
+      p->batch = 1;
+    }
+    if (p->X == nullptr) {
+      p->X = device_alloc(4 * p->slot_bytes, "workspace X");
+      p->Y = device_alloc(6 * p->slot_bytes, "workspace Y");
+    }
     p->G = device_alloc(p->slot_bytes, "workspace G");
     upload(p->tw, twiddles(p->n), p->fp64, nullptr);
     (void)amp_table(p);
@@ -218,20 +236,9 @@ void plan_reset(pin_plan p, void* F, uint8_t* ridx, hipStream_t s) {
   p->launch(KC_RESET, s, [&] { p->ops->reset(F, ridx, s); });
 }
 
-void plan_run_radii(pin_plan p, const void* dk, void* F, uint8_t* ridx, int r0, int r1, hipStream_t s) {
-  prep_hessian_input(p, dk, s);
-  for (int r = r0; r < r1; ++r) {
-    Range range("pin radius", p->n, r);
-    const void* w = p->window_row(r);
-    p->launch(KC_XPASS_HESS, s, [&] { p->ops->xpass(0, p->G, p->X, w, p->tw, 1.0, s); });
-    p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, s); });
-    p->launch(KC_ZPASS_COLLAPSE, s, [&] { p->ops->zpass_collapse(p->Y, p->tw, F, ridx, r, p->sphere_gain, s); });
-  }
-}
-
-size_t velocity_workspace_bytes(int n, bool fp64) {
+size_t velocity_workspace_bytes(int n, bool fp64, int batch) {
   const size_t rb = fp64 ? 8 : 4;
-  return 4 * (size_t)n * n * (n / 2) * 2 * rb;
+  return 4 * (size_t)batch * n * n * (n / 2) * 2 * rb;
 }
 
 void plan_reset_v(pin_plan p, void* F, uint8_t* ridx, void* vmax, hipStream_t s) {
@@ -239,25 +246,54 @@ void plan_reset_v(pin_plan p, void* F, uint8_t* ridx, void* vmax, hipStream_t s)
   p->launch(KC_ZERO, s, [&] { p->ops->zero(vmax, 3 * (size_t)p->n * p->n * p->n, s); });
 }
 
-void plan_run_radii_v(pin_plan p, const void* dk, void* F, uint8_t* ridx, void* vmax, int r0, int r1, hipStream_t s) {
-  if (p->V == nullptr) p->V = device_alloc(velocity_workspace_bytes(p->n, p->fp64), "workspace V");
-  const double vscale = p->box / (2.0 * 3.14159265358979323846);
+// Waves that fill the device in the z pass: two a SIMD.  Below that the radii of a batch are split
+// into groups that run side by side.
+constexpr int kZWavesWanted = 2048;
+
+void plan_run_radii(pin_plan p, const void* dk, void* F, uint8_t* ridx, void* vmax, int r0, int r1, bool fresh,
+                    hipStream_t s) {
+  const bool vel = vmax != nullptr;
+  const int most = vel && p->ops->batch_v < p->batch ? p->ops->batch_v : p->batch;
+  if (vel && p->V == nullptr) p->V = device_alloc(velocity_workspace_bytes(p->n, p->fp64, most), "workspace V");
   prep_hessian_input(p, dk, s);
-  for (int r = r0; r < r1; ++r) {
-    const void* w = p->window_row(r);
-    p->launch(KC_XPASS_HESS, s, [&] { p->ops->xpass(0, p->G, p->X, w, p->tw, 1.0, s); });
-    p->launch(KC_YPASS_VEL, s, [&] { p->ops->ypass_hess_grad(p->X, p->Y, p->V, p->tw, s); });
-    p->launch(KC_ZPASS_COLLAPSE_V, s, [&] {
-      p->ops->zpass_collapse_v(p->Y, p->V, p->tw, F, ridx, vmax, r, p->sphere_gain, vscale, s);
-    });
+  const int batches = (r1 - r0 + most - 1) / most;
+  for (int k = 0; k < batches; ++k) {
+    // batches of nearly equal counts, a whole call from the last radius to the first
+    const int i = fresh ? batches - 1 - k : k;
+    const int rb = r0 + (int)((long long)(r1 - r0) * i / batches);
+    const int nb = r0 + (int)((long long)(r1 - r0) * (i + 1) / batches) - rb;
+    Range range("pin radius", p->n, rb);
+    const void* w = p->window_row(rb);
+    p->launch(KC_XPASS_HESS, s, [&] { p->ops->xpass(0, p->G, p->X, w, p->tw, 1.0, nb, s); });
+    if (vel)
+      p->launch(KC_YPASS_VEL, s, [&] { p->ops->ypass_hess_grad(p->X, p->Y, p->V, p->tw, nb, s); });
+    else
+      p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, nb, s); });
+    CollapseStep c{};
+    c.in = p->Y;
+    c.gin = vel ? p->V : nullptr;
+    c.tw = p->tw;
+    c.F = F;
+    c.ridx = ridx;
+    c.vmax = vmax;
+    c.part = p->X;   // the y pass has read it
+    c.r0 = rb;
+    c.nb = nb;
+    const int want = (kZWavesWanted + p->ops->zwaves - 1) / p->ops->zwaves;
+    c.groups = vel || want <= 1 ? 1 : (want < nb ? want : nb);
+    c.whole = fresh;
+    c.fresh = fresh && k == 0;
+    c.sphere_gain = p->sphere_gain;
+    c.vscale = p->box / (2.0 * 3.14159265358979323846);
+    p->launch(vel ? KC_ZPASS_COLLAPSE_V : KC_ZPASS_COLLAPSE, s, [&] { p->ops->zcollapse(c, s); });
   }
 }
 
 void plan_deformation_tensor(pin_plan p, const void* dk, int r, void* T6, hipStream_t s) {
   const void* w = p->window_row(r < 0 ? p->nr_capacity : r);
   prep_hessian_input(p, dk, s);
-  p->launch(KC_XPASS_HESS, s, [&] { p->ops->xpass(0, p->G, p->X, w, p->tw, 1.0, s); });
-  p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, s); });
+  p->launch(KC_XPASS_HESS, s, [&] { p->ops->xpass(0, p->G, p->X, w, p->tw, 1.0, 1, s); });
+  p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, 1, s); });
   p->launch(KC_ZPASS_STORE, s, [&] { p->ops->zpass_store(6, p->Y, p->tw, T6, s); });
 }
 
@@ -267,8 +303,8 @@ void plan_displacements(pin_plan p, const void* dk, void* psi1, void* psi2, hipS
   const double lfac = p->box / (2.0 * 3.14159265358979323846);
   if (psi1) {
     // psi1(k) = i (L/2pi) f dk / f^2
-    p->launch(KC_XPASS_GRAD, s, [&] { p->ops->xpass(1, dk, p->X, nullptr, p->tw, lfac / n3, s); });
-    p->launch(KC_YPASS_GRAD, s, [&] { p->ops->ypass(1, p->X, p->Y, p->tw, s); });
+    p->launch(KC_XPASS_GRAD, s, [&] { p->ops->xpass(1, dk, p->X, nullptr, p->tw, lfac / n3, 1, s); });
+    p->launch(KC_YPASS_GRAD, s, [&] { p->ops->ypass(1, p->X, p->Y, p->tw, 1, s); });
     p->launch(KC_ZPASS_STORE, s, [&] { p->ops->zpass_store(3, p->Y, p->tw, psi1, s); });
   }
   if (psi2) {
@@ -276,13 +312,13 @@ void plan_displacements(pin_plan p, const void* dk, void* psi1, void* psi2, hipS
     // (3/7) i (L/2pi) f / f^2 and the inverse gradient transforms.
     prep_hessian_input(p, dk, s);
     const void* ones = p->window_row(p->nr_capacity);
-    p->launch(KC_XPASS_HESS, s, [&] { p->ops->xpass(0, p->G, p->X, ones, p->tw, 1.0, s); });
-    p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, s); });
+    p->launch(KC_XPASS_HESS, s, [&] { p->ops->xpass(0, p->G, p->X, ones, p->tw, 1.0, 1, s); });
+    p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, 1, s); });
     p->launch(KC_ZPASS_MU2, s, [&] { p->ops->zpass_mu2(p->Y, p->tw, p->xslot(0), nullptr, s); });
-    p->launch(KC_YPASS_FWD, s, [&] { p->ops->ypass(2, p->xslot(0), p->xslot(1), p->tw, s); });
+    p->launch(KC_YPASS_FWD, s, [&] { p->ops->ypass(2, p->xslot(0), p->xslot(1), p->tw, 1, s); });
     p->launch(KC_XPASS_FWDINV, s,
               [&] { p->ops->xpass_fwdinv(false, p->xslot(1), p->Y, p->tw, (3.0 / 7.0) * lfac / n3, s); });
-    p->launch(KC_YPASS_GRAD, s, [&] { p->ops->ypass(1, p->Y, p->X, p->tw, s); });
+    p->launch(KC_YPASS_GRAD, s, [&] { p->ops->ypass(1, p->Y, p->X, p->tw, 1, s); });
     p->launch(KC_ZPASS_STORE, s, [&] { p->ops->zpass_store(3, p->X, p->tw, psi2, s); });
   }
 }
@@ -302,22 +338,22 @@ void plan_lpt3_displacement(pin_plan p, const void* dk, void* psi3, hipStream_t 
   // along z into L[6]; forward y into L[7]
   prep_hessian_input(p, dk, s);
   const void* ones = p->window_row(p->nr_capacity);
-  p->launch(KC_XPASS_HESS, s, [&] { p->ops->xpass(0, p->G, p->X, ones, p->tw, 1.0, s); });
-  p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, s); });
+  p->launch(KC_XPASS_HESS, s, [&] { p->ops->xpass(0, p->G, p->X, ones, p->tw, 1.0, 1, s); });
+  p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, 1, s); });
   p->launch(KC_ZPASS_MU2_STORE, s, [&] { p->ops->zpass_mu2(p->Y, p->tw, lslot(6), lslot(0), s); });
-  p->launch(KC_YPASS_FWD, s, [&] { p->ops->ypass(2, lslot(6), lslot(7), p->tw, s); });
+  p->launch(KC_YPASS_FWD, s, [&] { p->ops->ypass(2, lslot(6), lslot(7), p->tw, 1, s); });
   // T2 (Hessian of phi2, lap phi2 = mu2): forward x, M / f^2 and the Hessian x outputs, then the
   // Hessian y pass; its z pass forms the third-order sources with T1 and transforms them forward
   // along z into L[6..9]
   p->launch(KC_XPASS_FWDINV_HESS, s, [&] { p->ops->xpass_fwdinv(true, lslot(7), p->X, p->tw, 1.0 / n3, s); });
-  p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, s); });
+  p->launch(KC_YPASS_HESS, s, [&] { p->ops->ypass(0, p->X, p->Y, p->tw, 1, s); });
   p->launch(KC_ZPASS_LPT3, s, [&] { p->ops->zpass_lpt3(p->Y, lslot(0), p->tw, lslot(6), s); });
   // sources forward along y into X[0..3], then forward x, the psi3 multipliers and the inverse
   // x transforms into Y[0..2], the inverse y (packed) into X and the inverse z into psi3
   for (int i = 0; i < 4; ++i)
-    p->launch(KC_YPASS_FWD, s, [&] { p->ops->ypass(2, lslot(6 + i), p->xslot(i), p->tw, s); });
+    p->launch(KC_YPASS_FWD, s, [&] { p->ops->ypass(2, lslot(6 + i), p->xslot(i), p->tw, 1, s); });
   p->launch(KC_XPASS_LPT3, s, [&] { p->ops->xpass_lpt3(p->X, p->Y, p->tw, lfac / n3, s); });
-  p->launch(KC_YPASS_LPT3, s, [&] { p->ops->ypass(4, p->Y, p->X, p->tw, s); });
+  p->launch(KC_YPASS_LPT3, s, [&] { p->ops->ypass(4, p->Y, p->X, p->tw, 1, s); });
   p->launch(KC_ZPASS_STORE, s, [&] { p->ops->zpass_store(3, p->X, p->tw, psi3, s); });
 }
 

@@ -70,7 +70,9 @@ extern const char* const kClassNames[KC_COUNT];
 
 bool size_supported(int n);
 void validate_desc(const pin_plan_desc* d);
-size_t workspace_bytes(int n, int n_radii, bool fp64);
+// Radii that one launch of each collapse pass takes on an N^3 grid, of at most n_radii.
+int collapse_batch(int n, int n_radii, bool fp64, bool vel);
+size_t workspace_bytes(int n, int n_radii, bool fp64, int batch);
 void check_device_range(const void* p, size_t bytes, const char* name);
 
 }  // namespace pin
@@ -92,10 +94,11 @@ struct pin_plan_s {
   // has generated fields for (a serving slot changes its box per request), oldest first
   std::vector<std::pair<double, void*>> amp_tables;
   void* wtab = nullptr;   // (nr_capacity + 1) rows of N window values
-  void* X = nullptr;      // 4 half slots (= 2 packed slots)
-  void* Y = nullptr;      // 6 half slots (= 3 packed slots)
+  int batch = 1;          // radii per launch of the collapse passes (collapse_batch)
+  void* X = nullptr;      // max(4, 3 batch) half slots
+  void* Y = nullptr;      // 6 half slots (= 3 packed slots) per radius of the batch
   void* G = nullptr;      // 1 half slot: the radius-independent Hessian input
-  void* V = nullptr;      // 4 half slots (= 2 packed slots) for v_max, allocated on first use
+  void* V = nullptr;      // 4 half slots (= 2 packed slots) per radius for v_max, allocated on first use
   pin::FragWorkspace frag;  // fragmentation workspace, allocated on first use
   void* L = nullptr;      // 10 half slots for the third-order displacement, allocated on first use:
                           // T1 as six real fields, then four source slots
@@ -134,20 +137,23 @@ struct pin_plan_s {
 
 namespace pin {
 
-// Create a plan for `desc` whose window table can later hold up to `radii_capacity` radii.
-pin_plan plan_create(const pin_plan_desc* desc, int radii_capacity);
+// Create a plan for `desc` whose window table can later hold up to `radii_capacity` radii and
+// whose collapse passes take `batch` radii a launch (one if that much memory is not there).
+pin_plan plan_create(const pin_plan_desc* desc, int radii_capacity, int batch);
 void plan_free(pin_plan p);
 // Replace the radii (strictly decreasing, <= capacity): window tables uploaded on `s`.
 void plan_set_radii(pin_plan p, const double* radii, int n_radii, hipStream_t s);
 
 void plan_generate_field(pin_plan p, uint64_t seed, void* dk, hipStream_t s);
 void plan_reset(pin_plan p, void* F, uint8_t* ridx, hipStream_t s);
-void plan_run_radii(pin_plan p, const void* dk, void* F, uint8_t* ridx, int r0, int r1, hipStream_t s);
-void plan_deformation_tensor(pin_plan p, const void* dk, int r, void* T6, hipStream_t s);
-// v_max variants: the reset also zeroes v_max [3][N^3]; the radii also record v_max
+// the v_max variant also zeroes v_max [3][N^3]
 void plan_reset_v(pin_plan p, void* F, uint8_t* ridx, void* vmax, hipStream_t s);
-void plan_run_radii_v(pin_plan p, const void* dk, void* F, uint8_t* ridx, void* vmax, int r0, int r1, hipStream_t s);
-size_t velocity_workspace_bytes(int n, bool fp64);
+// Radii [r0, r1) into the state (F, ridx), and v_max if vmax is not null.  fresh: all radii of the
+// plan from a reset state, which is not read.
+void plan_run_radii(pin_plan p, const void* dk, void* F, uint8_t* ridx, void* vmax, int r0, int r1, bool fresh,
+                    hipStream_t s);
+size_t velocity_workspace_bytes(int n, bool fp64, int batch);
+void plan_deformation_tensor(pin_plan p, const void* dk, int r, void* T6, hipStream_t s);
 void plan_displacements(pin_plan p, const void* dk, void* psi1, void* psi2, hipStream_t s);
 size_t lpt3_workspace_bytes(int n, bool fp64);
 void plan_lpt3_displacement(pin_plan p, const void* dk, void* psi3, hipStream_t s);

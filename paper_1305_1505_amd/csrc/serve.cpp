@@ -53,7 +53,7 @@ class HipExec {
   size_t slot_bytes(int n) const {
     const size_t rb = cfg_.prec == PIN_FP64 ? 8 : 4;
     const size_t vol = (size_t)n * n * n;
-    return workspace_bytes(n, kMaxRadii, cfg_.prec == PIN_FP64) + (size_t)n * n * (n / 2 + 1) * 2 * rb +
+    return workspace_bytes(n, kMaxRadii, cfg_.prec == PIN_FP64, 1) + (size_t)n * n * (n / 2 + 1) * 2 * rb +
            vol * (rb + 1) + 6 * vol * rb;
   }
 
@@ -64,7 +64,7 @@ class HipExec {
     auto* s = new HipSlot();
     try {
       s->n = n;
-      s->plan = plan_create(&d, kMaxRadii);
+      s->plan = plan_create(&d, kMaxRadii, 1);   // requests fill the device together
       const size_t rb = s->plan->real_bytes;
       const size_t vol = (size_t)n * n * n;
       hip_check(hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking), "hipStreamCreateWithFlags");
@@ -145,14 +145,13 @@ class HipExec {
   void set_error(const std::string& m) { set_last_error(m); }
 
  private:
-  // The seed-independent rest of the path (reset, every radius, displacements) as one graph on
-  // the slot's buffers; no memset nodes (the reset is a kernel).
+  // The seed-independent rest of the path (every radius, displacements) as one graph on the slot's
+  // buffers; kernel nodes only.
   hipGraphExec_t capture(Slot* s, int want_disp) {
     pin_plan p = s->plan;
     hip_check(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
     try {
-      plan_reset(p, s->F, s->ridx, s->stream);
-      plan_run_radii(p, s->dk, s->F, s->ridx, 0, p->nr, s->stream);
+      plan_run_radii(p, s->dk, s->F, s->ridx, nullptr, 0, p->nr, true, s->stream);
       if (want_disp) plan_displacements(p, s->dk, s->psi1, s->psi2, s->stream);
     } catch (...) {
       hipGraph_t g = nullptr;
