@@ -152,22 +152,24 @@ pin_status pin_plan_set_growth(pin_plan plan, double omega_m, hipStream_t stream
     check_plan(plan);
     if (!(omega_m > 0.0 && omega_m <= 1.0)) fail(PIN_ERR_INVALID_ARG, "omega_m must be in (0, 1]");
     const GrowthTable g = growth_table(omega_m);
-    std::vector<double> host(g.d);
-    host.insert(host.end(), g.dd.begin(), g.dd.end());
-    const size_t nd = host.size() * sizeof(double), ng = g.guide.size() * sizeof(int32_t);
-    std::vector<unsigned char> bytes(nd + ng);
-    std::memcpy(bytes.data(), host.data(), nd);
-    std::memcpy(bytes.data() + nd, g.guide.data(), ng);
+    // one block: D, dD/dy, the polynomials' space, the guide
+    const size_t nd = (size_t)kGrowthNodes * sizeof(double), np = (size_t)kMaxBuckets * kBucketStride * sizeof(double),
+                 ng = g.guide.size() * sizeof(int32_t);
+    std::vector<unsigned char> bytes(2 * nd + np + ng);
+    std::memcpy(bytes.data(), g.d.data(), nd);
+    std::memcpy(bytes.data() + nd, g.dd.data(), nd);
+    if (!g.poly.empty()) std::memcpy(bytes.data() + 2 * nd, g.poly.data(), g.poly.size() * sizeof(double));
+    std::memcpy(bytes.data() + 2 * nd + np, g.guide.data(), ng);
     if (plan->growth == nullptr) plan->growth = device_alloc(bytes.size(), "growth table");
     hip_check(hipMemcpyAsync(plan->growth, bytes.data(), bytes.size(), hipMemcpyHostToDevice, stream),
               "hipMemcpyAsync");
     hip_check(hipStreamSynchronize(stream), "hipStreamSynchronize");
-    plan->growth_y0 = g.y0;
-    plan->growth_h = g.h;
-    plan->growth_a_per_D = g.a_per_D;
-    plan->growth_lom = g.lambda_over_m;
-    plan->growth_gl0 = g.guide_l0;
-    plan->growth_ginv = g.guide_inv;
+    const double* d = static_cast<const double*>(plan->growth);
+    const double* poly = d + 2 * kGrowthNodes;
+    plan->growth_args = GrowthArgs{d, d + kGrowthNodes, kGrowthNodes, g.y0, g.h, g.a_per_D, g.lambda_over_m,
+                                   reinterpret_cast<const int32_t*>(poly + (size_t)kMaxBuckets * kBucketStride),
+                                   kGrowthGuide, (float)g.guide_l0, (float)g.guide_inv, poly, g.f_base, g.f_count,
+                                   g.e_base, g.e_count, g.f_inf, g.f_none};
   });
 }
 
@@ -179,13 +181,7 @@ pin_status pin_collapse_redshift(pin_plan plan, const void* F, size_t count, voi
     if (count > ((size_t)1 << 40)) fail(PIN_ERR_INVALID_ARG, "count is too large");
     check_device_range(F, count * plan->real_bytes, "F");
     check_device_range(zc, count * plan->real_bytes, "zc");
-    const double* d = static_cast<const double*>(plan->growth);
-    plan->launch(KC_REDSHIFT, stream, [&] {
-      plan->ops->redshift(F, count, d, d + kGrowthNodes, kGrowthNodes, plan->growth_y0, plan->growth_h,
-                          plan->growth_a_per_D, plan->growth_lom,
-                          reinterpret_cast<const int32_t*>(d + 2 * kGrowthNodes), kGrowthGuide, plan->growth_gl0,
-                          plan->growth_ginv, zc, stream);
-    });
+    plan->launch(KC_REDSHIFT, stream, [&] { plan->ops->redshift(F, count, plan->growth_args, zc, stream); });
   });
 }
 

@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <thread>
 
 namespace pin {
@@ -181,6 +182,91 @@ std::vector<double> radius_ladder(int n, double box, double r_max, double r_min,
   }
 }
 
+namespace {
+
+// 1 + z_c at F from the table: the node interval holding t = 1/F, then Newton steps on the cubic
+// Hermite interpolant of D(y) there.
+double one_plus_z(const GrowthTable& g, double F) {
+  const double t = 1.0 / F;
+  const int k = (int)(std::upper_bound(g.d.begin(), g.d.end(), t) - g.d.begin()) - 1;
+  const double d0 = g.d[k], d1 = g.d[k + 1], m0 = g.dd[k] * g.h, m1 = g.dd[k + 1] * g.h;
+  double s = (t - d0) / (d1 - d0);
+  for (int it = 0; it < 4; ++it) {
+    const double s2 = s * s, s3 = s2 * s;
+    const double hv = (2 * s3 - 3 * s2 + 1) * d0 + (s3 - 2 * s2 + s) * m0 + (-2 * s3 + 3 * s2) * d1 + (s3 - s2) * m1;
+    const double hp = (6 * s2 - 6 * s) * d0 + (3 * s2 - 4 * s + 1) * m0 + (-6 * s2 + 6 * s) * d1 + (3 * s2 - 2 * s) * m1;
+    s = std::fmin(1.0, std::fmax(0.0, s - (hv - t) / hp));
+  }
+  return std::exp(-(g.y0 + (k + s) * g.h));
+}
+
+int bucket_of(double x) {
+  uint64_t b;
+  std::memcpy(&b, &x, 8);
+  return (int)(b >> (52 - kBucketBits));
+}
+
+double bucket_start(int k) {
+  const uint64_t b = (uint64_t)k << (52 - kBucketBits);
+  double x;
+  std::memcpy(&x, &b, 8);
+  return x;
+}
+
+// 1 + z_c as a polynomial in the mantissa (less the bucket's centre) of its variable, per bucket of
+// 1/32 octave: of F from 2 / D_inf up, where it is close to a power of F, and of e = F - 1/D_inf
+// below, where D flattens and 1 + z_c goes as the square root of e.  Both are smooth over a
+// bucket's relative width, so interpolation at kBucketCoefs Chebyshev points reaches the table's own
+// error (1e-13 of D between its nodes); a bucket that is further than 8e-13 of D off between its
+// points gets NaN coefficients, which send its values to the search.
+void redshift_buckets(GrowthTable& g, double om, double ol, double d_inf) {
+  const double last = 1.0 / g.d[kGrowthNodes - 1], top = 1.0 / g.d[0];
+  g.f_none = last * (1.0 - 1e-9);
+  const bool flat = ol / om >= 1e-6;   // D has reached its limit at the table's end
+  const double f0 = ol == 0.0 ? last * 1.05 : 2.0 * (flat ? 1.0 / d_inf : last);
+  g.f_base = bucket_of(f0) + 1;
+  if (flat) {
+    g.f_inf = 1.0 / d_inf;
+    g.e_base = bucket_of(g.f_inf * 0x1p-16);
+    g.e_count = std::min(bucket_of(bucket_start(g.f_base) - g.f_inf) + 1 - g.e_base, kMaxBuckets / 2 + 64);
+  }
+  g.f_count = std::max(0, std::min(bucket_of(top) - g.f_base, kMaxBuckets - g.e_count));
+  const int n = kBucketCoefs;
+  g.poly.assign((size_t)(g.f_count + g.e_count) * kBucketStride, std::nan(""));
+  const double half = 0.5 / (1 << kBucketBits);
+  for (int k = 0; k < g.f_count + g.e_count; ++k) {
+    const bool in_f = k < g.f_count;
+    const int id = in_f ? g.f_base + k : g.e_base + k - g.f_count;
+    const double lo = bucket_start(id), octave = std::exp2(std::floor(std::log2(lo))), mid = lo / octave + half;
+    auto value = [&](double u) { return one_plus_z(g, (mid + u) * octave + (in_f ? 0.0 : g.f_inf)); };
+    if (!(bucket_start(id + 1) + (in_f ? 0.0 : g.f_inf) < top) || !(lo + (in_f ? 0.0 : g.f_inf) > last)) continue;
+    // divided differences at the Chebyshev points, then the monomial coefficients
+    long double x[kBucketCoefs], c[kBucketCoefs], a[kBucketCoefs] = {};
+    for (int i = 0; i < n; ++i) {
+      x[i] = half * std::cos(kPi * (i + 0.5) / n);
+      c[i] = value((double)x[i]);
+    }
+    for (int j = 1; j < n; ++j)
+      for (int i = n - 1; i >= j; --i) c[i] = (c[i] - c[i - 1]) / (x[i] - x[i - j]);
+    for (int i = n - 1; i >= 0; --i) {   // a <- a (u - x_i) + c_i
+      for (int j = n - 1; j > 0; --j) a[j] = a[j - 1] - x[i] * a[j];
+      a[0] = c[i] - x[i] * a[0];
+    }
+    double err = 0.0;
+    for (double u : {-0.97 * half, -0.4 * half, 0.1 * half, 0.6 * half, 0.97 * half}) {
+      double v = (double)a[n - 1];
+      for (int j = n - 2; j >= 0; --j) v = v * u + (double)a[j];
+      err = std::fmax(err, std::fabs(v / value(u) - 1.0));
+    }
+    // how far D is off for that error of 1 + z_c: towards the limit D ~ D_inf (1 - k (1 + z_c)^2)
+    const double cond = in_f ? 1.0 : std::fmin(1.0, 2.0 * lo / (lo + g.f_inf));
+    if (err * cond <= 8e-13)
+      for (int j = 0; j < n; ++j) g.poly[(size_t)k * kBucketStride + j] = (double)a[j];
+  }
+}
+
+}  // namespace
+
 GrowthTable growth_table(double om) {
   static const GaussLegendre gl;
   const double ol = 1.0 - om;
@@ -240,6 +326,9 @@ GrowthTable growth_table(double om) {
     while (node + 1 < kGrowthNodes && g.d[node + 1] <= tb) ++node;
     g.guide[b] = node;
   }
+  // D at a -> infinity: beyond a = 1e6 the integrand is ol^(-3/2) x^-3
+  const double d_inf = ol > 0.0 ? 2.5 * om * std::sqrt(ol) * (Iy[kGrowthNodes - 1] + 0.5e-12 * std::pow(ol, -1.5)) / norm : 0.0;
+  redshift_buckets(g, om, ol, d_inf);
   return g;
 }
 

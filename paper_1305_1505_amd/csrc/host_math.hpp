@@ -36,7 +36,16 @@ struct GrowthTable {
   std::vector<double> d, dd;
   std::vector<int32_t> guide;
   double guide_l0 = 0, guide_inv = 0;
+  // 1 + z_c as a polynomial per bucket (redshift_buckets)
+  std::vector<double> poly;   // kBucketCoefs per bucket, those in F first
+  int f_base = 0, f_count = 0, e_base = 0, e_count = 0;
+  double f_inf = 0;           // 1/D(a -> infinity): the e buckets are in e = F - f_inf
+  double f_none = 0;          // no collapse below this F
 };
+// Buckets of the collapse redshift: 2^kBucketBits per octave of their variable, kBucketCoefs
+// polynomial coefficients each, kBucketStride apart (odd, so that lanes of different buckets read
+// different LDS banks); at most kMaxBuckets, which fill 64 KB of LDS.
+constexpr int kBucketBits = 5, kBucketCoefs = 8, kBucketStride = 9, kMaxBuckets = 910;
 GrowthTable growth_table(double omega_m);
 // Amplitude A with sigma^2(8 Mpc/h) = sigma8^2.
 double amplitude_for_sigma8(double sigma8, double gamma, double ns);

@@ -157,15 +157,13 @@ void reset(void* F, uint8_t* ridx, hipStream_t s) {
   hipLaunchKernelGGL((k_reset<RR>), dim3(grid), dim3(block), 0, s, static_cast<RR*>(F), ridx, total);
 }
 
-void redshift(const void* F, size_t count, const double* d, const double* dd, int m, double y0, double h,
-              double a_per_D, double lambda_over_m, const int32_t* guide, int guide_count, double guide_l0,
-              double guide_inv, void* z, hipStream_t s) {
+void redshift(const void* F, size_t count, const GrowthArgs& g, void* z, hipStream_t s) {
   if (count == 0) return;
-  GrowthArgs g{d, dd, m, y0, h, a_per_D, lambda_over_m, guide, guide_count, (float)guide_l0, (float)guide_inv};
-  const int block = 256;
-  const int grid = (int)((count + block - 1) / block);
-  hipLaunchKernelGGL((k_redshift<RR>), dim3(grid), dim3(block), 0, s, static_cast<const RR*>(F), count, g,
-                     static_cast<RR*>(z));
+  constexpr size_t span = (size_t)kRedshiftThreads * kRedshiftValues;
+  const size_t need = (count + span - 1) / span, most = 512;   // two workgroups on each of 256 CUs
+  const size_t lds = (size_t)(g.f_count + g.e_count) * kBucketStride * sizeof(double);
+  hipLaunchKernelGGL((k_redshift<RR>), dim3((unsigned)(need < most ? need : most)), dim3(kRedshiftThreads), lds, s,
+                     static_cast<const RR*>(F), count, g, static_cast<RR*>(z));
 }
 
 void zero(void* p, size_t count, hipStream_t s) {

@@ -30,6 +30,8 @@
 
 #include "collapse_dev.hpp"
 #include "fft_core.hpp"
+#include "host_math.hpp"
+#include "ops.hpp"
 
 namespace pin {
 
@@ -1223,59 +1225,99 @@ __global__ void k_reset(R* __restrict__ F, uint8_t* __restrict__ ridx, size_t co
 
 // ---------------------------------------------------------------------------------------------
 // Collapse redshift: z_c with D(z_c) = 1/F, D the growing mode normalised to 1 at z = 0,
-// tabulated (float64) on y = ln a at m nodes y0 + i h with D and dD/dy.  The interval holding
-// 1/F is found by bisection on the monotone D, then y by Newton steps on the cubic Hermite
-// interpolant of D(y) there.  Below the first node D = a (1 - (2/11)(Lambda/Om) a^3 + ...) / a_per_D
-// is inverted directly; F <= 0, or 1/F beyond the last node (a > 1e6), gives z_c = -1.
-struct GrowthArgs {
-  const double* d;
-  const double* dd;
-  int m;
-  double y0, h, a_per_D, lambda_over_m;
-  const int32_t* guide;   // last node with d <= 2^(l0 + b / inv), per bucket b < k
-  int k;
-  float l0, inv;
-};
+// tabulated (float64) on y = ln a at m nodes y0 + i h with D and dD/dy.  F <= 0, or 1/F beyond the
+// last node (a > 1e6), gives z_c = -1.
+//
+// 1 + z_c is read from a polynomial per bucket of 1/32 octave of F, or of e = F - 1/D_inf towards
+// the no-collapse limit, whose coefficients the host fits to the table's inverse (float64): an
+// index from the variable's leading bits, 64 bytes of coefficients from LDS, 7 fused multiply-adds.
+// Values outside the buckets take the search: the interval holding 1/F by bisection on the monotone
+// D, then y by Newton steps on the cubic Hermite interpolant of D(y) there; below the first node
+// D = a (1 - (2/11)(Lambda/Om) a^3 + ...) / a_per_D is inverted directly.  The search for every
+// value (a chain of dependent loads, three float64 divisions and an exponential) took 179 us for
+// the 256^3 values of a float32 grid, 0.75 TB/s of its 8 bytes a value; with the buckets 42 us,
+// 3.2 TB/s (128 us with the coefficients gathered through L1, four cache lines a value).
+// z_c by search, for f >= f_none
+__device__ __forceinline__ double redshift_search(const GrowthArgs& g, double f) {
+  const double t = 1.0 / f;
+  if (t < g.d[0]) {
+    const double a0 = t * g.a_per_D;
+    const double a = a0 * (1.0 + (2.0 / 11.0) * g.lambda_over_m * a0 * a0 * a0);
+    return 1.0 / a - 1.0;
+  }
+  if (!(t < g.d[g.m - 1])) return -1.0;
+  // the bucket of t in log2 narrows the node search to a few steps; the bounds are checked
+  // against t so that a bucket taken one off by rounding only widens the search
+  int b = (int)((__log2f((float)t) - g.l0) * g.inv);
+  b = min(max(b, 0), g.k - 2);
+  int lo = g.guide[b], hi = min(g.guide[b + 1] + 1, g.m - 1);   // d[lo] <= t < d[hi]
+  if (!(g.d[lo] <= t)) lo = 0;
+  if (!(t < g.d[hi])) hi = g.m - 1;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (g.d[mid] <= t) lo = mid; else hi = mid;
+  }
+  const double d0 = g.d[lo], d1 = g.d[hi], m0 = g.dd[lo] * g.h, m1 = g.dd[hi] * g.h;
+  // Newton on the cubic Hermite segment from the chord: the chord is within h/4 of the root
+  // in s, and each step squares the error times about h, so three steps reach rounding
+  double s = (t - d0) / (d1 - d0);
+#pragma unroll
+  for (int it = 0; it < 3; ++it) {
+    const double s2 = s * s, s3 = s2 * s;
+    const double hv = (2 * s3 - 3 * s2 + 1) * d0 + (s3 - 2 * s2 + s) * m0 + (-2 * s3 + 3 * s2) * d1 + (s3 - s2) * m1;
+    const double hp = (6 * s2 - 6 * s) * d0 + (3 * s2 - 4 * s + 1) * m0 + (-6 * s2 + 6 * s) * d1 + (3 * s2 - 2 * s) * m1;
+    s = fmin(1.0, fmax(0.0, s - (hv - t) / hp));
+  }
+  return exp(-(g.y0 + (lo + s) * g.h)) - 1.0;
+}
+
+constexpr int kRedshiftThreads = 1024;   // two workgroups a CU: 64 KB of LDS and 64 VGPRs a thread
+constexpr int kRedshiftValues = 4;       // a thread's values in flight, a workgroup's apart
 
 template <typename R>
-__global__ void k_redshift(const R* __restrict__ F, size_t count, GrowthArgs g, R* __restrict__ z) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const double f = (double)F[i];
-  double out = -1.0;
-  if (f > 0.0) {
-    const double t = 1.0 / f;
-    if (t < g.d[0]) {
-      const double a0 = t * g.a_per_D;
-      const double a = a0 * (1.0 + (2.0 / 11.0) * g.lambda_over_m * a0 * a0 * a0);
-      out = 1.0 / a - 1.0;
-    } else if (t < g.d[g.m - 1]) {
-      // the bucket of t in log2 narrows the node search to a few steps; the bounds are checked
-      // against t so that a bucket taken one off by rounding only widens the search
-      int b = (int)((__log2f((float)t) - g.l0) * g.inv);
-      b = min(max(b, 0), g.k - 2);
-      int lo = g.guide[b], hi = min(g.guide[b + 1] + 1, g.m - 1);   // d[lo] <= t < d[hi]
-      if (!(g.d[lo] <= t)) lo = 0;
-      if (!(t < g.d[hi])) hi = g.m - 1;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (g.d[mid] <= t) lo = mid; else hi = mid;
-      }
-      const double d0 = g.d[lo], d1 = g.d[hi], m0 = g.dd[lo] * g.h, m1 = g.dd[hi] * g.h;
-      // Newton on the cubic Hermite segment from the chord: the chord is within h/4 of the root
-      // in s, and each step squares the error times about h, so three steps reach rounding
-      double s = (t - d0) / (d1 - d0);
+__global__ void __launch_bounds__(kRedshiftThreads)
+__attribute__((amdgpu_waves_per_eu(8)))
+k_redshift(const R* __restrict__ F, size_t count, GrowthArgs g, R* __restrict__ z) {
+  extern __shared__ __align__(16) double s_poly[];
+  for (int i = threadIdx.x; i < (g.f_count + g.e_count) * kBucketStride; i += kRedshiftThreads) s_poly[i] = g.poly[i];
+  __syncthreads();
+  constexpr int SPAN = kRedshiftThreads * kRedshiftValues;
+#pragma unroll 1
+  for (size_t i0 = (size_t)blockIdx.x * SPAN + threadIdx.x; i0 < count; i0 += (size_t)gridDim.x * SPAN) {
+    R f[kRedshiftValues];
 #pragma unroll
-      for (int it = 0; it < 3; ++it) {
-        const double s2 = s * s, s3 = s2 * s;
-        const double hv = (2 * s3 - 3 * s2 + 1) * d0 + (s3 - 2 * s2 + s) * m0 + (-2 * s3 + 3 * s2) * d1 + (s3 - s2) * m1;
-        const double hp = (6 * s2 - 6 * s) * d0 + (3 * s2 - 4 * s + 1) * m0 + (-6 * s2 + 6 * s) * d1 + (3 * s2 - 2 * s) * m1;
-        s = fmin(1.0, fmax(0.0, s - (hv - t) / hp));
+    for (int k = 0; k < kRedshiftValues; ++k) {
+      const size_t i = i0 + k * kRedshiftThreads;
+      f[k] = F[i < count ? i : i0];
+    }
+#pragma unroll
+    for (int k = 0; k < kRedshiftValues; ++k) {
+      // bucket of F, else of e
+      const double fk = (double)f[k], e = fk - g.f_inf;
+      const unsigned bf = (unsigned)(__double2hiint(fk) >> (20 - kBucketBits)) - (unsigned)g.f_base;
+      const unsigned be = (unsigned)(__double2hiint(e) >> (20 - kBucketBits)) - (unsigned)g.e_base;
+      const bool in_f = bf < (unsigned)g.f_count, in_e = be < (unsigned)g.e_count;
+      double out = -1.0;
+      if (fk >= g.f_none) {
+        out = __builtin_nan("");
+        if (in_f || in_e) {
+          const double x = in_f ? fk : e;
+          const double* c = s_poly + kBucketStride * (in_f ? bf : g.f_count + be);
+          const int hi = (__double2hiint(x) & 0xFFFFF) | 0x3FF00000;
+          const double mid =
+              __hiloint2double((hi & ~((1 << (20 - kBucketBits)) - 1)) | (1 << (19 - kBucketBits)), 0);
+          const double u = __hiloint2double(hi, __double2loint(x)) - mid;
+          double v = c[kBucketCoefs - 1];
+#pragma unroll
+          for (int j = kBucketCoefs - 2; j >= 0; --j) v = fma(v, u, c[j]);
+          out = v - 1.0;
+        }
+        if (!(out == out)) out = redshift_search(g, fk);
       }
-      out = exp(-(g.y0 + (lo + s) * g.h)) - 1.0;
+      const size_t i = i0 + k * kRedshiftThreads;
+      if (i < count) z[i] = (R)out;
     }
   }
-  z[i] = (R)out;
 }
 
 template <typename R>

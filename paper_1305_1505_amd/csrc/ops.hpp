@@ -29,6 +29,20 @@ struct CollapseStep {
   double sphere_gain, vscale;
 };
 
+// Growing-mode tables of the collapse redshift, on the device (host_math.hpp: GrowthTable).
+struct GrowthArgs {
+  const double* d;
+  const double* dd;
+  int m;
+  double y0, h, a_per_D, lambda_over_m;
+  const int32_t* guide;   // last node with d <= 2^(l0 + b / inv), per bucket b < k
+  int k;
+  float l0, inv;
+  const double* poly;     // kBucketStride values per bucket: f_count of F, then e_count of e
+  int f_base, f_count, e_base, e_count;
+  double f_inf, f_none;
+};
+
 struct SizeOps {
   int n;
   bool fp64;
@@ -67,10 +81,8 @@ struct SizeOps {
   // the field of `seed`, mode amplitudes from the plan's table (mode_amplitudes)
   void (*grf)(void* dk, uint64_t seed, const double* amp, hipStream_t s);
   void (*reset)(void* F, uint8_t* ridx, hipStream_t s);
-  // collapse redshift of count F values (growth table on the device, see k_redshift)
-  void (*redshift)(const void* F, size_t count, const double* d, const double* dd, int m, double y0, double h,
-                   double a_per_D, double lambda_over_m, const int32_t* guide, int guide_count, double guide_l0,
-                   double guide_inv, void* z, hipStream_t s);
+  // collapse redshift of count F values (growth tables on the device, see k_redshift)
+  void (*redshift)(const void* F, size_t count, const GrowthArgs& g, void* z, hipStream_t s);
   // count reals of the plan's precision set to zero
   void (*zero)(void* p, size_t count, hipStream_t s);
   // per-point collapse model on [6][count] tensors

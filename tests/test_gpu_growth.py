@@ -95,3 +95,24 @@ def test_redshift_dense_sweep(lib, om):
     idx = np.flatnonzero(ok)[np.linspace(0, ok.sum() - 1, 40).astype(int)]
     resid = np.array([growth.growth(1.0 / (1.0 + z[i]), om) * F[i] - 1.0 for i in idx])
     assert np.max(np.abs(resid)) <= 1e-12
+
+
+@pytest.mark.parametrize("om,count", [(0.25, 1), (0.25, 257), (1.0, 1023), (0.999999, 1025)])
+def test_redshift_bucket_edges(lib, om, count):
+    """Values on both sides of the buckets' edges (1/32 octave of F, and of F - 1/D_inf towards the
+    no-collapse limit), at counts around a workgroup's 1024: D(z_c) F = 1 with the oracle's D within
+    the documented 1e-12, besides the float64 rounding of z_c."""
+    import torch
+
+    plan = lib.Plan(16, 10.0, [1.0], prec=lib.PIN_FP64)
+    plan.set_growth(om)
+    limit = 1.0 / growth.growth_limit(om) if om < 1.0 else 0.0
+    edge = 2.0 ** np.arange(-12, 10)[:, None] * (1 + np.arange(0, 32, 3) / 32.0)
+    edge = np.concatenate([edge.ravel(), limit + edge.ravel()])
+    F = np.concatenate([np.nextafter(edge, 0.0), edge, np.nextafter(edge, np.inf)])
+    F = np.resize(np.random.default_rng(1).permutation(F[F > limit * (1 + 1e-4)]), count)
+    z = plan.collapse_redshift(torch.tensor(F, dtype=torch.float64, device="cuda")).cpu().numpy()
+    plan.close()
+    some = np.unique(np.linspace(0, count - 1, 60).astype(int))
+    for i in some:
+        assert abs(growth.growth(1.0 / (1.0 + z[i]), om) * F[i] - 1.0) <= 1e-12 + 2.0 ** -52 / (1.0 + z[i]), (F[i], z[i])
