@@ -58,7 +58,12 @@ __device__ __forceinline__ int xcd_tile(int b, int nblocks) {
 }
 
 constexpr int round_up64(int x) { return (x + 63) / 64 * 64; }
-constexpr int strided_threads(int nb0) { return round_up64(nb0 < 1024 ? nb0 : 1024); }
+// one butterfly a thread up to 1024; above, the most threads that share the butterflies evenly
+// (1536 at N = 384 and 768: 768 threads with two each, not 1024 of which half have two)
+constexpr int strided_threads(int nb0) {
+  const int turns = (nb0 + 1023) / 1024;
+  return round_up64((nb0 + turns - 1) / turns);
+}
 constexpr int pow2_floor(int x) {
   int p = 1;
   while (p * 2 <= x) p *= 2;
@@ -76,15 +81,23 @@ struct Strided {
   using E0 = Engine<V, N, PS, 1, true, 64, DIR>;
   static constexpr int T = strided_threads(E0::nb(E0::R0));
   using E = Engine<V, N, PS, 1, true, T, DIR>;
-  // occupancy target (waves per SIMD): two 1024-thread workgroups per CU for float32 tiles where
-  // each thread owns one butterfly and the transform ends in registers (the x and y passes keep
-  // one transform's data live, within 64 VGPRs); otherwise 4 (float64 tiles are LDS-bound there)
-  static constexpr int WPE = (sizeof(V) == 8 && E::K0 == 1 && E::SAME && E::max_held() <= E::R0) ? 8 : 4;
-  // the float64 x pass keeps three outputs' multipliers and a transform live: at 4 waves per SIMD
-  // it spills; 2 waves (1.37 -> 1.21 ms at 512^3).  The float32 Hessian x pass of workgroups
+  // occupancy target (least waves per SIMD), float32 tiles of at most 8 values a thread at either
+  // end: two workgroups per CU (8 waves per SIMD of 64 VGPRs at 1024 threads, 6 of 80 at 768: with
+  // one workgroup of 1024, 384^3 took 0.235 ms in the x and 0.532 in the y pass, 0.213 and 0.450
+  // with two of 768); otherwise 4 (float64 tiles are LDS-bound there)
+  static constexpr int WPE = sizeof(V) != 8 || !E::SAME ? 4 : E::max_held() <= 8 ? 8 : E::K0 > 1 && E::K0 * E::R0 <= 8 ? T / 128 : 4;
+  // the float64 x pass keeps three outputs' multipliers and a transform live: held to 4 waves per
+  // SIMD it spilled with masked stages, so 2 are asked for; without the masks it needs 108 VGPRs and
+  // runs 4 (512^3: 1.20 ms at 2, 0.84 at 4).  The float32 Hessian x pass of workgroups
   // under 1024 threads (64^3, 256^3: 64 bytes a lane at 64 VGPRs, which made the 256^3 pass
   // fetch 5.6x its input) gets 6 waves per SIMD (80 VGPRs; three 512-thread workgroups a CU).
   static constexpr int XWPE = sizeof(V) == 16 ? 2 : (WPE == 8 && T < 1024 ? 6 : WPE);
+  // float32 tiles of more than 8 values a thread (768^3) leave room for one workgroup per CU, whose
+  // loads, transforms and stores nothing else overlaps: the y pass then holds a pair's input in
+  // registers for both its transforms and loads the next one while the second runs (768^3: 4.36 ->
+  // 4.05 ms; the x pass, bound by its strided writes, gained nothing from holding its input).
+  // 1024 threads have no registers left for it (1024^3: 52 spilled).
+  static constexpr bool HOLD = sizeof(V) == 8 && E::K0 * E::R0 > 8 && T < 1024;
   static constexpr int GRID = N * NZT;
   static constexpr size_t HSLOT = (size_t)N * N * HZ;
 };
@@ -228,7 +241,7 @@ __global__ void k_prep(const typename Cplx<R>::type* __restrict__ dk, typename C
 // wait for each one before issuing the next.
 template <typename R, int N, int MODE>
 __global__ void __launch_bounds__((Strided<R, N, +1>::T))
-__attribute__((amdgpu_waves_per_eu(Strided<R, N, +1>::XWPE, Strided<R, N, +1>::XWPE)))
+__attribute__((amdgpu_waves_per_eu(Strided<R, N, +1>::XWPE)))
 k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* __restrict__ out,
         const R* __restrict__ wtab, const typename Cplx<R>::type* __restrict__ tw, R scale) {
   using S = Strided<R, N, +1>;
@@ -537,7 +550,7 @@ template <class RC> constexpr int last_pair(int a) {
 
 template <typename R, int N, int RECIPE>
 __global__ void __launch_bounds__((Strided<R, N, +1>::T))
-__attribute__((amdgpu_waves_per_eu(Strided<R, N, +1>::WPE, Strided<R, N, +1>::WPE)))
+__attribute__((amdgpu_waves_per_eu(Strided<R, N, +1>::WPE)))
 k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* __restrict__ out,
                const typename Cplx<R>::type* __restrict__ tw, typename Cplx<R>::type* __restrict__ out2) {
   using S = Strided<R, N, +1>;
@@ -569,6 +582,25 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
     zz[k] = z;
     jj[k] = j;
   }
+  // HOLD: the pair's first input stays in registers for both signs, and the next pair's is loaded
+  // while the pair's last transform runs
+  constexpr bool HOLD = S::HOLD;
+  V held[HOLD ? E::K0 : 1][HOLD ? E::R0 : 1];
+  auto hold = [&](int q) {
+    if constexpr (HOLD) {
+#pragma unroll
+      for (int k = 0; k < E::K0; ++k) {
+        unsigned off = (unsigned)(jj[k] * HZ + (ok[k] ? zz[k] : 0));
+        asm volatile("" : "+v"(off));
+#pragma unroll
+        for (int s = 0; s < E::R0; ++s) {
+          const V* p = in + RC::A[2 * q] * S::HSLOT + ((size_t)x * N + s * M) * HZ + off;
+          held[k][s] = RC::STREAM && q == last_pair<RC>(RC::A[2 * q]) ? ld_stream(p) : *p;
+        }
+      }
+    }
+  };
+  hold(0);
   // One transform per (pair, sign): u = fy^bA fz^cA X_aA + sgn i fy^bB fz^cB X_aB.  By
   // linearity sgn = +1 gives C[kz] = A + iB and sgn = -1 gives conj(C[N - kz]) = A - iB.  Each
   // transform reads its inputs itself (L2 hits after the first read of a tile) so that only one
@@ -607,7 +639,11 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
           const bool last_a = RC::STREAM && final_sgn && q == last_pair<RC>(aa);
           const bool last_b = RC::STREAM && final_sgn && q == last_pair<RC>(ab);
           const V* pa = in + aa * S::HSLOT + ubase + off;
-          const V xa = ok[k] ? (last_a ? ld_stream(pa) : *pa) : V{R(0), R(0)};
+          V xa;
+          if constexpr (HOLD)
+            xa = held[k][s];
+          else
+            xa = ok[k] ? (last_a ? ld_stream(pa) : *pa) : V{R(0), R(0)};
           V ta = cscale(xa, powf_int(fy, RC::B[ca]) * powf_int(fz, RC::C[ca]));
           if (RC::ti(ca)) ta = V{-ta.y, ta.x};
           if (has_b) {
@@ -621,6 +657,7 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
           }
         }
       }
+      if (HOLD && q + 1 < RC::Q && (sgn < 0 || !has_b)) hold(q + 1);
       E::run(u, lds, s_tw, t);
 #pragma unroll
       for (int k = 0; k < E::K0; ++k)
