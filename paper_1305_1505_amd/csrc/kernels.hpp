@@ -9,7 +9,8 @@
 //         P[k]       = C[k]       k in [0, N/2)
 //         P[N/2 + k] = C[N - k]   k in [1, N/2)     (= conj(A[k]) + i conj(B[k]))
 //       (P[N/2], the Nyquist term, is zero and is neither written nor read), so that both halves
-//       are written as aligned runs by the y pass and the z pass loads each element once.
+//       are written as aligned runs by the y pass and the z pass loads each element once.  A slot
+//       of one real output (B = 0) holds the first half only.
 //   real field              [N][N][N]
 //
 // Inverse 3D transform of the six Hessian components with shared prefixes.  With
@@ -614,7 +615,7 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
     V* dst = (RC::SPLIT > 0 && q >= RC::SPLIT) ? out2 + (size_t)(q - RC::SPLIT) * PSLOT : out + (size_t)q * PSLOT;
 #pragma unroll
     for (int sgn = 1; sgn >= -1; sgn -= 2) {
-      if (!has_b && sgn < 0) break;   // B = 0: C[N - kz] = conj(C[kz]), written below
+      if (!has_b && sgn < 0) break;   // B = 0: C[N - kz] = conj(C[kz]), formed by the z pass
       // opaque copies of the indices: the compiler would otherwise compute every transform's
       // multipliers and addresses up front and keep them live across all of them
       int jv[E::K0], zv[E::K0];
@@ -672,7 +673,13 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
                 reinterpret_cast<V*>(plane + (unsigned)L::index(0, jv[k] + s * M, zv[k] + HZ) * (unsigned)sizeof(V));
             if (sgn > 0) {
               st_slot<R, N, SLOTS>(first, u[k][s]);
-              if (!has_b && zv[k] > 0) st_slot<R, N, SLOTS>(second, conj(u[k][s]));
+              // the conjugate that a slot of one component leaves to the z pass stays an operand:
+              // without it the last butterfly's products would be contracted into its sums where
+              // they were not, and the gradient would round differently
+              if (!has_b && zv[k] > 0) {
+                const V w = conj(u[k][s]);
+                asm volatile("" ::"v"(w.x), "v"(w.y));
+              }
             } else if (zv[k] > 0) {
               st_slot<R, N, SLOTS>(second, conj(u[k][s]));
             }
@@ -760,7 +767,7 @@ template <typename R, int N, int P> struct ZLoader {
   static_assert(R0 % 2 == 0 && M0 * (R0 / 2) == HZ, "z pass: the first half of the elements is n < N/2");
   static_assert((size_t)3 * N * N * sizeof(V) < ((size_t)1 << 32), "z pass: plane offsets must fit 32 bits");
   size_t plane;
-  unsigned o_lo, o_ny, o_hi;
+  unsigned o_lo, o_ny, o_hi, o_rev;
   bool ny;
 
   __device__ __forceinline__ ZLoader(int line, int j) {
@@ -770,7 +777,24 @@ template <typename R, int N, int P> struct ZLoader {
     o_lo = (unsigned)L::index(0, ly, j) * (unsigned)sizeof(V);
     o_ny = (unsigned)L::index(0, ly, j == 0 ? HZ : N - j) * (unsigned)sizeof(V);
     o_hi = (unsigned)L::index(0, ly, 3 * HZ - j) * (unsigned)sizeof(V);
+    o_rev = (unsigned)L::index(0, ly, M0 - j) * (unsigned)sizeof(V);
     ny = j == 0;
+  }
+  // A slot of one real component: C[N - k] = conj(C[k]), so only the first half is there, and the
+  // second, n = N - ((R0 - s) M0 - j), is the first read backwards from the same cache lines.
+  __device__ __forceinline__ void load_one(const V* slot, V (&dst)[R0]) const {
+    const char* base = reinterpret_cast<const char*>(slot + plane);
+#pragma unroll
+    for (int s = 0; s < R0 / 2; ++s) dst[s] = *reinterpret_cast<const V*>(base + (o_lo + s * STEPB));
+#pragma unroll
+    for (int s = R0 / 2; s < R0; ++s) {
+      const V x = *reinterpret_cast<const V*>(base + (o_rev + (R0 - 1 - s) * STEPB));
+      // opaque: the transform then takes the sign as it takes any loaded value, and contracts and
+      // rounds as it does for a slot of two components
+      R y = -x.y;
+      asm("" : "+v"(y));
+      dst[s] = s == R0 / 2 && ny ? V{R(0), R(0)} : V{x.x, y};
+    }
   }
   __device__ __forceinline__ void load(const V* slot, V (&dst)[R0]) const {
     const char* base = reinterpret_cast<const char*>(slot + plane);
@@ -830,7 +854,11 @@ k_zpass(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R>::t
   const int lineL = line_ok ? line : Z::LINES - 1;
   const ZLoader<R, N, P> ld(lineL, j);
 #pragma unroll
-  for (int q = 0; q < Q; ++q) ld.load(in + (size_t)q * PSLOT, v[q]);
+  for (int q = 0; q < Q; ++q)
+    if (Q == 2 && q == 1)
+      ld.load_one(in + (size_t)q * PSLOT, v[q]);   // x y | z
+    else
+      ld.load(in + (size_t)q * PSLOT, v[q]);
   if constexpr (Z::ZT::QL == Q) {
     E::run(v, lds, s_tw, t);
   } else {
@@ -1180,7 +1208,7 @@ k_zcollapse(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R
         const V* gin = static_cast<const V*>(args.gin) + (size_t)2 * b * PSLOT;
         V w[2][R0];
         ld.load(gin, w[0]);
-        ld.load(gin + PSLOT, w[1]);
+        ld.load_one(gin + PSLOT, w[1]);
 #pragma unroll
         for (int c = 0; c < 2; ++c) E::run(*reinterpret_cast<V(*)[1][R0]>(&w[c]), lds, s_tw, tt);
         const R vs = (R)args.vscale;
