@@ -31,10 +31,10 @@ void xpass(int mode, const void* dk, void* out, const void* wtab, const void* tw
            hipStream_t s) {
   using S = Strided<RR, NN, +1>;
   if (mode == 0) {
-    hipLaunchKernelGGL((k_xpass<RR, NN, 0>), dim3(S::GRID, nb), dim3(S::T), 0, s, static_cast<const VV*>(dk),
+    hipLaunchKernelGGL((k_xpass<RR, NN, 0>), dim3(S::GRID, nb, S::SPLIT ? 3 : 1), dim3(S::T), 0, s, static_cast<const VV*>(dk),
                        static_cast<VV*>(out), static_cast<const RR*>(wtab), static_cast<const VV*>(tw), (RR)scale);
   } else {
-    hipLaunchKernelGGL((k_xpass<RR, NN, 1>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(dk),
+    hipLaunchKernelGGL((k_xpass<RR, NN, 1>), dim3(S::GRID, 1, S::SPLIT ? 2 : 1), dim3(S::T), 0, s, static_cast<const VV*>(dk),
                        static_cast<VV*>(out), static_cast<const RR*>(nullptr), static_cast<const VV*>(tw), (RR)scale);
   }
 }
@@ -59,19 +59,19 @@ void xpass_lpt3(const void* in, void* out, const void* tw, double scale, hipStre
 void ypass(int recipe, const void* in, void* out, const void* tw, int nb, hipStream_t s) {
   if (recipe == 0) {
     using S = Strided<RR, NN, +1>;
-    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 0>), dim3(S::GRID, nb), dim3(S::T), 0, s, static_cast<const VV*>(in),
+    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 0>), dim3(S::GRID, nb, S::SPLIT ? YRecipe<0>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
                        static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
   } else if (recipe == 1) {
     using S = Strided<RR, NN, +1>;
-    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 1>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(in),
+    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 1>), dim3(S::GRID, 1, S::SPLIT ? YRecipe<1>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
                        static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
   } else if (recipe == 3) {
     using S = Strided<RR, NN, +1>;
-    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 3>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(in),
+    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 3>), dim3(S::GRID, 1, S::SPLIT ? YRecipe<3>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
                        static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
   } else if (recipe == 4) {
     using S = Strided<RR, NN, +1>;
-    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 4>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(in),
+    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 4>), dim3(S::GRID, 1, S::SPLIT ? YRecipe<4>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
                        static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
   } else {
     using S = Strided<RR, NN, -1>;
@@ -83,7 +83,7 @@ void ypass(int recipe, const void* in, void* out, const void* tw, int nb, hipStr
 // Hessian (3 packed slots to out) and v_max gradient (2 packed slots to gout) in one y pass.
 void ypass_hess_grad(const void* in, void* out, void* gout, const void* tw, int nb, hipStream_t s) {
   using S = Strided<RR, NN, +1>;
-  hipLaunchKernelGGL((k_ypass_packed<RR, NN, 5>), dim3(S::GRID, nb), dim3(S::T), 0, s, static_cast<const VV*>(in),
+  hipLaunchKernelGGL((k_ypass_packed<RR, NN, 5>), dim3(S::GRID, nb, S::SPLIT ? YRecipe<5>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
                      static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(gout));
 }
 

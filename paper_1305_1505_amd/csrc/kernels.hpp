@@ -99,6 +99,11 @@ struct Strided {
   // 4.05 ms; the x pass, bound by its strided writes, gained nothing from holding its input).
   // 1024 threads have no registers left for it (1024^3: 52 spilled).
   static constexpr bool HOLD = sizeof(V) == 8 && E::K0 * E::R0 > 8 && T < 1024;
+  // small grids: the x pass's outputs and the y pass's pairs are workgroups of their own
+  // (blockIdx.z) instead of one's turns, of which each waits for its loads and barriers (32^3
+  // float32, 8 radii: x pass 10.9 -> 7.0 us, y pass 9.2 -> 6.6; at 64^3 the launches are full
+  // without it: 183 us against 186 with it for 16 float64 radii)
+  static constexpr bool SPLIT = N <= 48;
   static constexpr int GRID = N * NZT;
   static constexpr size_t HSLOT = (size_t)N * N * HZ;
 };
@@ -261,6 +266,7 @@ k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* _
   const int zt = bt % S::NZT;
   const int y = bt / S::NZT;
   const int fy = ifreq(y, N);
+  const int a0 = S::SPLIT ? blockIdx.z : 0, a1 = S::SPLIT ? a0 + 1 : NA;   // this workgroup's outputs
   if constexpr (MODE == 0 && E::K0 == 1) {
     // Hessian, one butterfly per thread: same values as the general form below, in a form whose
     // schedule (data loads batched, the window loads kept out of that batch) measured 13% faster
@@ -272,7 +278,7 @@ k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* _
     ok = ok && z < HZ;
     const R wyz = ok ? wtab[y] * wtab[z] : R(1);
 #pragma unroll 1
-    for (int a = 0; a < NA; ++a) {
+    for (int a = a0; a < a1; ++a) {
       V u[1][E::R0];
 #pragma unroll
       for (int s = 0; s < E::R0; ++s) {
@@ -310,7 +316,7 @@ k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* _
   // One output at a time: the input tile is read again for each output (an L2 hit after the
   // first), so that only one transform's data is live and two workgroups fit on a CU.
 #pragma unroll 1
-  for (int a = 0; a < NA; ++a) {
+  for (int a = a0; a < a1; ++a) {
     V u[E::K0][E::R0];
 #pragma unroll
     for (int k = 0; k < E::K0; ++k) {
@@ -608,6 +614,7 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
   // transform's data is live and two workgroups fit on a CU; the outputs are streamed past L2.
 #pragma unroll
   for (int q = 0; q < RC::Q; ++q) {
+    if (S::SPLIT && q != (int)blockIdx.z) continue;
     const int ca = 2 * q, cb = 2 * q + 1;
     const bool has_b = cb < RC::NC;
     const int aa = RC::A[ca];
@@ -1246,14 +1253,22 @@ __global__ void k_merge(const R* __restrict__ Fg, const uint8_t* __restrict__ rg
   R f = fresh ? R(0) : F[i];
   const int before = whole ? 256 : -1;
   int r = before;
-  for (int k = 0; k < groups; ++k) {
-    const size_t e = (size_t)k * vol + i;
-    const R fk = Fg[e];
-    const int rk = rg[e];   // 255: this group left the state as it was
-    if (rk != 255 && (fk > f || (fk == f && rk < r))) {
-      f = fk;
-      r = rk;
+  // eight groups' values at a time, all loaded before any is compared
+  for (int k0 = 0; k0 < groups; k0 += 8) {
+    R fk[8];
+    int rk[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const size_t e = (size_t)(k0 + k < groups ? k0 + k : groups - 1) * vol + i;
+      fk[k] = Fg[e];
+      rk[k] = rg[e];   // 255: this group left the state as it was
     }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (rk[k] != 255 && (fk[k] > f || (fk[k] == f && rk[k] < r))) {
+        f = fk[k];
+        r = rk[k];
+      }
   }
   if (r != before || fresh) {
     F[i] = f;

@@ -1,11 +1,11 @@
 // Collapse times without device allocation (pin_collapse_times_noalloc).
 //
-// The same launches as pin_collapse_times on a plan (reset, then per radius the Hessian x, y and
-// collapse z passes), but everything a plan would allocate -- the 11 half-spectrum workspace
-// slots, the twiddle table and the window table -- lives in one file-scope device array.  Host
+// The same launches as pin_collapse_times on a plan, but everything a plan would allocate -- the
+// half-spectrum workspace slots, the twiddle table and the window table -- lives in one file-scope
+// device array.  Host
 // code never passes that array's name to a kernel: its device address comes from
 // hipGetSymbolAddress, once per device, and only that address is used.  Tables are written on
-// the caller's stream by two small kernels (twiddles computed on the host in extended precision
+// the caller's stream by a small kernel (twiddles computed on the host in extended precision
 // and passed by value, windows computed on the device in float64), so the call queues kernels
 // only: no allocation, no copy from host memory, no host wait.
 #include <hip/hip_runtime.h>
@@ -58,20 +58,20 @@ struct WindowArgs {
   int n, nr;
 };
 
+// Both tables in one launch: the twiddles, then the windows W(kR) = exp(-k^2 R^2 / 2) on integer
+// frequencies f = 0..N/2-1, -N/2..-1, a row per radius.
 template <typename R>
-__global__ void k_noalloc_twiddles(R* tw, TwiddleArgs a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 2 * a.n) tw[i] = (R)a.v[i];
-}
-
-// W(kR) = exp(-k^2 R^2 / 2) on integer frequencies f = 0..N/2-1, -N/2..-1, row per radius
-template <typename R>
-__global__ void k_noalloc_windows(R* w, WindowArgs a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n * a.nr) return;
-  const int r = i / a.n, j = i - r * a.n;
-  const double f = j < a.n / 2 ? j : j - a.n;
-  const double kr = 2.0 * 3.14159265358979323846264338327950288 * f * a.radius[r] / a.n;
+__global__ void k_noalloc_tables(R* tw, TwiddleArgs a, R* w, WindowArgs b) {
+  int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 2 * a.n) {
+    tw[i] = (R)a.v[i];
+    return;
+  }
+  i -= 2 * a.n;
+  if (i >= b.n * b.nr) return;
+  const int r = i / b.n, j = i - r * b.n;
+  const double f = j < b.n / 2 ? j : j - b.n;
+  const double kr = 2.0 * 3.14159265358979323846264338327950288 * f * b.radius[r] / b.n;
   w[i] = (R)exp(-0.5 * kr * kr);
 }
 
@@ -85,12 +85,9 @@ void write_tables(void* tw, void* wtab, const pin_plan_desc* d, hipStream_t s) {
   wa.n = d->n;
   wa.nr = d->n_radii;
   const int block = 256;
-  hipLaunchKernelGGL(k_noalloc_twiddles<R>, dim3((2 * d->n + block - 1) / block), dim3(block), 0, s,
-                     static_cast<R*>(tw), ta);
-  hip_check(hipGetLastError(), "k_noalloc_twiddles");
-  hipLaunchKernelGGL(k_noalloc_windows<R>, dim3((d->n * d->n_radii + block - 1) / block), dim3(block), 0, s,
-                     static_cast<R*>(wtab), wa);
-  hip_check(hipGetLastError(), "k_noalloc_windows");
+  hipLaunchKernelGGL(k_noalloc_tables<R>, dim3((2 * d->n + d->n * d->n_radii + block - 1) / block), dim3(block), 0, s,
+                     static_cast<R*>(tw), ta, static_cast<R*>(wtab), wa);
+  hip_check(hipGetLastError(), "k_noalloc_tables");
 }
 
 }  // namespace
