@@ -43,7 +43,19 @@ constexpr int kFilament = -1;
 // Order positions considered per round: at 512^3 (z = 0) 2^16, 2^17, 2^18, 2^19 and 2^20 took
 // 191, 150, 134, 137 and 148 ms, with identical labels for every size (each figure then included
 // ~37 ms of host quadrature for the sigma nodes, now computed once per plan).
+// A round lasts as long as its dependent loads (at 256^3 a commit of 2^14 positions takes 46 us,
+// one of 2^18 53): hence no launch between rounds only to advance the head, a halo's sums in
+// registers over a step, independent loads issued together and labels that follow their halos
+// (512^3 95.5 -> 87.9 ms, 256^3 27.5 -> 25.5, 128^3 14.4 -> 11.3, 64^3 6.2 -> 5.8).
 constexpr int kWindow = 1 << 18;
+// words of ctl: error, participants, halos, selected, mergers, overflow; per round in turn the
+// earliest waiting particle (three) and the head (two)
+constexpr int kCtlError = 2, kCtlCount = 3, kCtlHalos = 4, kCtlSelected = 5, kCtlMergers = 6, kCtlOverflow = 7;
+constexpr int kCtlWait = 8, kCtlHead = 11, kCtlWords = 16;
+// With fewer participants than this half the window is better: the rounds then follow from the
+// busiest halo's steps, not from the window (128^3, 0.7 M participants: 13.5 ms a call with 2^18,
+// 11.4 with 2^17; 256^3, 5.4 M: 25.5 and 25.6).
+constexpr int kSmallOrder = 4 << 20;
 constexpr int kRoundsPerCheck = 32;    // rounds queued between host checks of progress
 constexpr int kRadiusTable = 1 << 20;  // halo radii tabulated for N_h up to this
 constexpr int kNodesPerOctave = 64;
@@ -91,7 +103,7 @@ __device__ __forceinline__ int find_root(const Dev& d, int h) {
     if (p == h) return h;
     h = p;
   }
-  d.ctl[2] = 1;   // not reachable with union by size; reported as an error by the host
+  d.ctl[kCtlError] = 1;   // not reachable with union by size; reported as an error by the host
   return h;
 }
 
@@ -149,23 +161,66 @@ __global__ void k_state_init(size_t vol, int32_t* label, int32_t* parent, int32_
   res_halo[i] = ~0ull;
 }
 
-__global__ void k_reserve(Dev d, unsigned long long hi) {
+// First order position of round r: the earliest particle that waited in the round before, or the
+// end of that round's window.  Counters in turn: the commits of round r - 1 take the minimum in
+// wait[r % 3], round r reads it, and clears the one of the round after the next.
+__device__ __forceinline__ int head_of(const Dev& d, unsigned r) {
+  return min(d.ctl[kCtlWait + r % 3], min(d.ctl[kCtlHead + (r + 1) % 2] + d.window, d.m));
+}
+
+__global__ void k_reserve(Dev d, unsigned r) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  const int p = d.ctl[0] + k;
+  const int head = head_of(d, r);
+  const int p = head + k;
   if (k >= d.window || p >= d.m) return;
+  const unsigned long long hi = (unsigned long long)(0xFFFFFFFFu - r) << 32;
   const int i = d.order[p];
   if (d.label[i] != kNotCollapsed) return;   // committed in an earlier round
   const unsigned long long key = hi | (unsigned)p;
-  int nb[6];
-  neighbours(i, d.n, nb);
-  reserve(&d.res_cell[i], key);
+  // The rounds are bound by the latency of dependent loads, so those that do not depend on each
+  // other are issued together: the words of the seven cells, then each level of the six trees.
+  int cell[7];
+  {
+    int nb[6];
+    neighbours(i, d.n, nb);
+    cell[6] = i;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) cell[c] = nb[c];
+  }
+  unsigned long long held[7];
+  int h[6], l[6];
+#pragma unroll
+  for (int c = 0; c < 7; ++c) held[c] = __hip_atomic_load(&d.res_cell[cell[c]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) h[c] = l[c] = d.label[cell[c]];
+#pragma unroll
+  for (int c = 0; c < 7; ++c)
+    if (held[c] > key) atomicMin(&d.res_cell[cell[c]], key);
+  bool climbing = true;
+  for (int it = 0; climbing; ++it) {
+    int up[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) up[c] = d.parent[h[c] >= 0 ? h[c] : i];
+    climbing = false;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      climbing = climbing || (h[c] >= 0 && up[c] != h[c]);
+      h[c] = h[c] >= 0 ? up[c] : h[c];
+    }
+    if (it > kFindLimit) {
+      d.ctl[kCtlError] = 1;   // not reachable with union by size; reported as an error by the host
+      break;
+    }
+  }
   int hl[6];
   int hc = 0;
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
-    reserve(&d.res_cell[nb[c]], key);
-    const int l = d.label[nb[c]];
-    if (l >= 0) insert_sorted(hl, hc, find_root(d, l));
+    if (h[c] < 0) continue;
+    // the member's label follows its halo: no halo merges while reservations are made, and any
+    // ancestor is a right label, so that concurrent readers see one whichever they read
+    if (h[c] != l[c]) d.label[cell[c]] = h[c];
+    insert_sorted(hl, hc, h[c]);
   }
   int32_t* it = d.items + (size_t)k * 7;
   it[0] = hc;
@@ -207,8 +262,8 @@ struct Step {
     const double nh = (double)d.hn[h];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      const double c = q[a] + d.hs[(size_t)a * d.vol + h] / nh;
-      x[a] = c + D * (d.hs[(size_t)(3 + a) * d.vol + h] / nh);
+      const double c = q[a] + d.hs[6 * (size_t)h + a] / nh;
+      x[a] = c + D * (d.hs[6 * (size_t)h + 3 + a] / nh);
     }
   }
   __device__ double dist(const double (&a)[3], const double (&b)[3]) const {
@@ -219,17 +274,34 @@ struct Step {
     const double r = radius(d.hn[h]);
     return dd < d.prm.fa * r + d.prm.fra + d.prm.fs * pow(r * sigma(r) * D, 1.7);
   }
-  __device__ void add(int h, int j, const double (&u)[3]) const {
-    d.hn[h] += 1;
+};
+
+// A halo's count and sums, held in registers over the additions of one step (in the order the
+// method makes them): one load and one store of its words instead of a dependent pair per particle.
+struct Sums {
+  int n;
+  double s[6];
+  __device__ __forceinline__ Sums(const Dev& d, int h) {
+    n = d.hn[h];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) s[a] = d.hs[6 * (size_t)h + a];
+  }
+  __device__ __forceinline__ void add(const Step& st, int h, int j, const double (&u)[3]) {
+    n += 1;
     double qj[3], qh[3];
-    coords(j, qj);
-    coords(h, qh);
+    st.coords(j, qj);
+    st.coords(h, qh);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      d.hs[(size_t)a * d.vol + h] = d.hs[(size_t)a * d.vol + h] + wrap(qj[a] - qh[a]);
-      d.hs[(size_t)(3 + a) * d.vol + h] = d.hs[(size_t)(3 + a) * d.vol + h] + u[a];
+      s[a] = s[a] + st.wrap(qj[a] - qh[a]);
+      s[3 + a] = s[3 + a] + u[a];
     }
-    d.label[j] = h;
+    st.d.label[j] = h;
+  }
+  __device__ __forceinline__ void store(const Dev& d, int h) const {
+    d.hn[h] = n;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) d.hs[6 * (size_t)h + a] = s[a];
   }
 };
 
@@ -248,19 +320,24 @@ __device__ void execute(const Dev& d, const R* F, const R* v, int p, int i, cons
   load_u(v, d.vol, i, d.uscale, ui);
 #pragma unroll
   for (int a = 0; a < 3; ++a) xi[a] = q[a] + st.D * ui[a];
-  bool has_fil = false;
+  unsigned fil = 0;   // the neighbours (six different cells) that are filament particles
 #pragma unroll
-  for (int c = 0; c < 6; ++c) has_fil = has_fil || d.label[nb[c]] == kFilament;
+  for (int c = 0; c < 6; ++c) fil |= d.label[nb[c]] == kFilament ? 1u << c : 0u;
+  const bool has_fil = fil != 0;
 
   auto accrete = [&](int h) {
-    st.add(h, i, ui);
-    for (int c = 0; c < 6; ++c) {
-      if (d.label[nb[c]] == kFilament) {
-        double uj[3];
-        load_u(v, d.vol, nb[c], d.uscale, uj);
-        st.add(h, nb[c], uj);
-      }
+    Sums sums(d, h);
+    sums.add(st, h, i, ui);
+    for (unsigned m = fil; m != 0; m &= m - 1) {
+      const int c = __ffs(m) - 1;
+      int j = nb[0];
+#pragma unroll
+      for (int e = 1; e < 6; ++e) j = c == e ? nb[e] : j;
+      double uj[3];
+      load_u(v, d.vol, j, d.uscale, uj);
+      sums.add(st, h, j, uj);
     }
+    sums.store(d, h);
   };
   auto best_halo = [&](const int* list, int cnt, double& best_d) {
     int best = -1;
@@ -284,8 +361,8 @@ __device__ void execute(const Dev& d, const R* F, const R* v, int p, int i, cons
     d.hn[i] = 1;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      d.hs[(size_t)a * d.vol + i] = 0.0;
-      d.hs[(size_t)(3 + a) * d.vol + i] = ui[a];
+      d.hs[6 * (size_t)i + a] = 0.0;
+      d.hs[6 * (size_t)i + 3 + a] = ui[a];
     }
     d.label[i] = i;
   } else if (hc == 0) {                            // (iv) filaments only
@@ -316,7 +393,7 @@ __device__ void execute(const Dev& d, const R* F, const R* v, int p, int i, cons
           const bool keep_a = d.hn[ha] > d.hn[hb] || (d.hn[ha] == d.hn[hb] && ha <= hb);
           const int keep = keep_a ? ha : hb, gone = keep_a ? hb : ha;
           // merger event, tagged with its place in the sequential order (particle, pair)
-          const int e = atomicAdd(&d.ctl[6], 1);
+          const int e = atomicAdd(&d.ctl[kCtlMergers], 1);
           if (e < (int)d.vol) {
             d.ev_key[e] = ((unsigned long long)p << 8) | (unsigned)(a * 8 + b);
             d.ev_f[e] = (double)F[i];
@@ -325,7 +402,7 @@ __device__ void execute(const Dev& d, const R* F, const R* v, int p, int i, cons
             d.ev_ids[4 * (size_t)e + 2] = d.hn[keep];
             d.ev_ids[4 * (size_t)e + 3] = d.hn[gone];
           } else {
-            d.ctl[7] = 1;
+            d.ctl[kCtlOverflow] = 1;
           }
           double qk[3], qg[3];
           st.coords(keep, qk);
@@ -334,9 +411,9 @@ __device__ void execute(const Dev& d, const R* F, const R* v, int p, int i, cons
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             const double off = st.wrap(qg[c] - qk[c]);
-            d.hs[(size_t)c * d.vol + keep] = d.hs[(size_t)c * d.vol + keep] + d.hs[(size_t)c * d.vol + gone] + ng * off;
-            d.hs[(size_t)(3 + c) * d.vol + keep] =
-                d.hs[(size_t)(3 + c) * d.vol + keep] + d.hs[(size_t)(3 + c) * d.vol + gone];
+            d.hs[6 * (size_t)keep + c] = d.hs[6 * (size_t)keep + c] + d.hs[6 * (size_t)gone + c] + ng * off;
+            d.hs[6 * (size_t)keep + 3 + c] =
+                d.hs[6 * (size_t)keep + 3 + c] + d.hs[6 * (size_t)gone + 3 + c];
           }
           d.hn[keep] += d.hn[gone];
           d.parent[gone] = keep;
@@ -359,36 +436,43 @@ __device__ void execute(const Dev& d, const R* F, const R* v, int p, int i, cons
 }
 
 template <typename R>
-__global__ void k_commit(Dev d, unsigned long long hi, const R* __restrict__ F, const R* __restrict__ v) {
+__global__ void k_commit(Dev d, unsigned r, const R* __restrict__ F, const R* __restrict__ v) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  const int p = d.ctl[0] + k;
+  const int head = head_of(d, r);
+  if (k == 0) {
+    d.ctl[kCtlHead + r % 2] = head;
+    d.ctl[kCtlWait + (r + 2) % 3] = 0x7FFFFFFF;
+  }
+  const int p = head + k;
   if (k >= d.window || p >= d.m) return;
+  const unsigned long long hi = (unsigned long long)(0xFFFFFFFFu - r) << 32;
   const int i = d.order[p];
   if (d.label[i] != kNotCollapsed) return;
   const unsigned long long key = hi | (unsigned)p;
   int nb[6];
   neighbours(i, d.n, nb);
+  // independent loads together, as in the reservations
   const int32_t* it = d.items + (size_t)k * 7;
   const int hc = it[0];
   int halos[6];
   bool own = d.res_cell[i] == key;
 #pragma unroll
-  for (int c = 0; c < 6; ++c) own = own && d.res_cell[nb[c]] == key;
-  for (int j = 0; j < hc; ++j) {
-    halos[j] = it[1 + j];
-    own = own && d.res_halo[halos[j]] == key;
+  for (int c = 0; c < 6; ++c) own &= d.res_cell[nb[c]] == key;
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    const int h = it[1 + j];
+    halos[j] = j < hc ? h : i;
+  }
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    const unsigned long long r = d.res_halo[halos[j]];
+    own &= j >= hc || r == key;
   }
   if (!own) {
-    atomicMin(&d.ctl[1], p);
+    atomicMin(&d.ctl[kCtlWait + (r + 1) % 3], p);
     return;
   }
   execute<R>(d, F, v, p, i, nb, halos, hc);
-}
-
-__global__ void k_advance(int32_t* ctl, int m, int window) {
-  const int head = ctl[1];
-  ctl[0] = head;
-  ctl[1] = head + window < m ? head + window : m;
 }
 
 // Final labels (the root of each member's halo), halo sizes at the roots, and the number of roots
@@ -443,9 +527,9 @@ __global__ void k_catalog(const int32_t* __restrict__ id, const int32_t* __restr
   nh_out[k] = hn[h];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const double c = q[a] + hs[(size_t)a * vol + h] / nh;
+    const double c = q[a] + hs[6 * (size_t)h + a] / nh;
     centre[(size_t)a * capacity + k] = (c - nd * floor(c / nd)) * cell;
-    disp[(size_t)a * capacity + k] = hs[(size_t)(3 + a) * vol + h] / nh * cell;
+    disp[(size_t)a * capacity + k] = hs[6 * (size_t)h + 3 + a] / nh * cell;
   }
 }
 
@@ -566,7 +650,7 @@ int fragment_run(FragWorkspace& w, bool fp64, int n, const void* F, const void* 
   const int block = 256;
   const int grid = (int)((vol + block - 1) / block);
   w.n_halos = -1;   // no catalogue until this run completes
-  hip_check(hipMemsetAsync(w.ctl, 0, 64, s), "hipMemsetAsync");
+  hip_check(hipMemsetAsync(w.ctl, 0, kCtlWords * 4, s), "hipMemsetAsync");
   if (fp64) {
     hipLaunchKernelGGL(k_keys<double>, dim3(grid), dim3(block), 0, s, static_cast<const double*>(F), vol, f_min,
                        w.keys[0], w.vals[0]);
@@ -580,13 +664,13 @@ int fragment_run(FragWorkspace& w, bool fp64, int n, const void* F, const void* 
   size_t tmp = w.sort_tmp_bytes;
   hip_check(hipcub::DeviceRadixSort::SortPairs(w.sort_tmp, tmp, kb, vb, (int)vol, 0, fp64 ? 64 : 32, s),
             "radix sort");
-  hipLaunchKernelGGL(k_count, dim3(1), dim3(1), 0, s, kb.Current(), vol, fp64 ? ~0ull : 0xFFFFFFFFull, w.ctl + 3);
+  hipLaunchKernelGGL(k_count, dim3(1), dim3(1), 0, s, kb.Current(), vol, fp64 ? ~0ull : 0xFFFFFFFFull, w.ctl + kCtlCount);
   hipLaunchKernelGGL(k_state_init, dim3(grid), dim3(block), 0, s, vol, label, w.parent, w.hn, w.res_cell,
                      w.res_halo);
   hip_check(hipGetLastError(), "fragmentation init");
   hip_check(hipMemcpyAsync(w.host_ctl, w.ctl, 16, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
   hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-  const int m = w.host_ctl[3];
+  const int m = w.host_ctl[kCtlCount];
 
   Dev d{};
   d.n = n;
@@ -611,11 +695,11 @@ int fragment_run(FragWorkspace& w, bool fp64, int n, const void* F, const void* 
   d.ev_key = w.ev_key;
   d.ev_f = w.ev_f;
   d.ev_ids = w.ev_ids;
-  const int window = kWindow;
+  const int window = m <= kSmallOrder ? kWindow / 2 : kWindow;
   d.window = window;
-  // head = 0, next head = end of the first window
-  const int32_t init[2] = {0, m < window ? m : window};
-  hip_check(hipMemcpyAsync(w.ctl, init, sizeof(init), hipMemcpyHostToDevice, s), "hipMemcpyAsync");
+  // round 0 starts at position 0: it reads wait[0] = 0 (and head[1] = 0); wait[1] takes its minimum
+  const int32_t init[5] = {0, 0x7FFFFFFF, 0x7FFFFFFF, 0, 0};
+  hip_check(hipMemcpyAsync(w.ctl + kCtlWait, init, sizeof(init), hipMemcpyHostToDevice, s), "hipMemcpyAsync");
   hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
 
   const int wgrid = window / block;
@@ -624,34 +708,34 @@ int fragment_run(FragWorkspace& w, bool fp64, int n, const void* F, const void* 
   const unsigned long long max_rounds = (unsigned long long)m + 2 * kRoundsPerCheck;
   while (m > 0) {
     for (int r = 0; r < kRoundsPerCheck; ++r, ++round) {
-      const unsigned long long hi = (0xFFFFFFFFull - round) << 32;
-      hipLaunchKernelGGL(k_reserve, dim3(wgrid), dim3(block), 0, s, d, hi);
+      hipLaunchKernelGGL(k_reserve, dim3(wgrid), dim3(block), 0, s, d, (unsigned)round);
       if (fp64) {
-        hipLaunchKernelGGL(k_commit<double>, dim3(wgrid), dim3(block), 0, s, d, hi, static_cast<const double*>(F),
-                           static_cast<const double*>(v));
+        hipLaunchKernelGGL(k_commit<double>, dim3(wgrid), dim3(block), 0, s, d, (unsigned)round,
+                           static_cast<const double*>(F), static_cast<const double*>(v));
       } else {
-        hipLaunchKernelGGL(k_commit<float>, dim3(wgrid), dim3(block), 0, s, d, hi, static_cast<const float*>(F),
-                           static_cast<const float*>(v));
+        hipLaunchKernelGGL(k_commit<float>, dim3(wgrid), dim3(block), 0, s, d, (unsigned)round,
+                           static_cast<const float*>(F), static_cast<const float*>(v));
       }
-      hipLaunchKernelGGL(k_advance, dim3(1), dim3(1), 0, s, w.ctl, m, window);
     }
     hip_check(hipGetLastError(), "fragmentation rounds");
-    hip_check(hipMemcpyAsync(w.host_ctl, w.ctl, 16, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
+    hip_check(hipMemcpyAsync(w.host_ctl, w.ctl, kCtlWords * 4, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
     hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-    if (w.host_ctl[2] != 0) fail(PIN_ERR_DEVICE, "fragmentation: halo tree deeper than expected");
-    if (w.host_ctl[0] >= m) break;
+    if (w.host_ctl[kCtlError] != 0) fail(PIN_ERR_DEVICE, "fragmentation: halo tree deeper than expected");
+    // the head that the next round would start at
+    const int end = std::min(w.host_ctl[kCtlHead + (round + 1) % 2] + window, m);
+    if (end == m && w.host_ctl[kCtlWait + round % 3] >= m) break;
     if (round > max_rounds) fail(PIN_ERR_DEVICE, "fragmentation made no progress");
   }
   // per-block root counts into the (now free) key buffer, then their sum
   int32_t* block_count = reinterpret_cast<int32_t*>(w.keys[0]);
   hipLaunchKernelGGL(k_finish, dim3(grid), dim3(block), 0, s, d, halo_size, block_count);
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(1024), 0, s, block_count, grid, w.ctl + 4);
+  hipLaunchKernelGGL(k_sum, dim3(1), dim3(1024), 0, s, block_count, grid, w.ctl + kCtlHalos);
   hip_check(hipGetLastError(), "fragmentation finish");
   hip_check(hipMemcpyAsync(w.host_ctl, w.ctl, 32, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
   hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-  if (w.host_ctl[7] != 0) fail(PIN_ERR_DEVICE, "fragmentation: merger events exceed the grid size");
-  w.n_halos = w.host_ctl[4];
-  w.n_mergers = w.host_ctl[6];
+  if (w.host_ctl[kCtlOverflow] != 0) fail(PIN_ERR_DEVICE, "fragmentation: merger events exceed the grid size");
+  w.n_halos = w.host_ctl[kCtlHalos];
+  w.n_mergers = w.host_ctl[kCtlMergers];
   w.n = n;
   return w.n_halos;
 }
@@ -686,17 +770,17 @@ int fragment_catalog(FragWorkspace& w, double cell, int32_t* id, int32_t* nh, do
   hip_check(hipGetLastError(), "catalogue flags");
   size_t tmp = w.sort_tmp_bytes;
   hip_check(hipcub::DeviceSelect::Flagged(w.sort_tmp, tmp, hipcub::CountingInputIterator<int32_t>(0), flags, id,
-                                          w.ctl + 5, (int)vol, s),
+                                          w.ctl + kCtlSelected, (int)vol, s),
             "catalogue select");
   const int cgrid = (w.n_halos + block - 1) / block;
   if (cgrid > 0) {
-    hipLaunchKernelGGL(k_catalog, dim3(cgrid), dim3(block), 0, s, id, w.ctl + 5, w.n, vol, w.hn, w.hs, cell, capacity,
+    hipLaunchKernelGGL(k_catalog, dim3(cgrid), dim3(block), 0, s, id, w.ctl + kCtlSelected, w.n, vol, w.hn, w.hs, cell, capacity,
                        nh, centre, disp);
     hip_check(hipGetLastError(), "catalogue");
   }
   hip_check(hipMemcpyAsync(w.host_ctl, w.ctl, 32, hipMemcpyDeviceToHost, s), "hipMemcpyAsync");
   hip_check(hipStreamSynchronize(s), "hipStreamSynchronize");
-  if (w.host_ctl[5] != w.n_halos) fail(PIN_ERR_DEVICE, "catalogue: halo count differs from the fragmentation's");
+  if (w.host_ctl[kCtlSelected] != w.n_halos) fail(PIN_ERR_DEVICE, "catalogue: halo count differs from the fragmentation's");
   return w.n_halos;
 }
 

@@ -26,11 +26,11 @@ struct FragWorkspace {
   size_t sort_tmp_bytes = 0;
   int32_t* parent = nullptr;
   int32_t* hn = nullptr;
-  double* hs = nullptr;           // [6][vol]: sums of offsets (3) and of displacements (3)
+  double* hs = nullptr;           // [vol][6]: sums of offsets (3) and of displacements (3)
   unsigned long long* res_cell = nullptr;
   unsigned long long* res_halo = nullptr;
   int32_t* items = nullptr;       // per window slot: count + up to 6 halo ids
-  int32_t* ctl = nullptr;         // head, next head, error, participants, halos, selected, mergers, overflow
+  int32_t* ctl = nullptr;         // counters (kCtl* words in fragment.hip)
   unsigned long long* ev_key = nullptr;  // merger events: (order position << 8 | pair), capacity vol
   double* ev_f = nullptr;                // F of the particle whose step merged
   int32_t* ev_ids = nullptr;             // keep, gone, N_keep before, N_gone
