@@ -188,11 +188,14 @@ template <typename R, int N> constexpr int slots_fit(int count) {
   return (int)(((size_t)256 << 20) / (count * (size_t)N * N * (N / 2) * 2 * sizeof(R)));
 }
 
-// Store into a slot between two passes: plain where one radius's slots (9 half slots, 13 with v_max)
-// fit the last-level cache and the next pass finds them there, streamed past the caches otherwise
-// (plain at 192^3 float32: x pass 34 -> 37 us, y pass 70 -> 62, z pass 54 -> 52; where the slots do
-// not fit streaming is the faster: 1.04 -> 1.01 ms for the 512^3 y pass, and at 192^3 float32 with
-// v_max, 368 MB, plain stores made the z pass 116 -> 138 us).
+// Store into a slot between two passes: plain where the SLOTS half slots that matter to its next
+// reader fit the last-level cache, streamed past the caches otherwise.  y-pass outputs count a
+// radius's 9 half slots (13 with v_max), x-pass outputs their own 3, the forward y pass's and the
+// 2LPT source's 2, the prepared input itself and the x pass's outputs.  Measured: y-pass outputs
+// plain at 192^3 float32 (9 fit), y pass 70 -> 62 us, z pass 54 -> 52, but with v_max (13 do not)
+// z pass 116 -> 138 us; x-pass outputs plain at 256^3 float32 (3 fit, 9 do not), x pass 63 -> 59 us,
+// y pass 139 -> 112, z pass 100 -> 121 (it waits for their write-back), collapse over 20 radii
+// 5.98 -> 5.78 ms, with v_max 8.49 -> 8.01; at 512^3 streaming is the faster (y pass 1.04 -> 1.01).
 template <typename R, int N, int SLOTS = 9, typename V> __device__ __forceinline__ void st_slot(V* p, V v) {
   if constexpr (slots_fit<R, N>(SLOTS) > 0) *p = v; else st_stream(p, v);
 }
@@ -234,7 +237,7 @@ __global__ void k_prep(const typename Cplx<R>::type* __restrict__ dk, typename C
       out = V{d.x * m, d.y * m};
     }
   }
-  st_slot<R, N>(&g0[PrepLayout<R, N>::index(x, y, z)], out);
+  st_slot<R, N, 4>(&g0[PrepLayout<R, N>::index(x, y, z)], out);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -295,7 +298,7 @@ k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* _
       // while the y pass runs (y pass 1.04 -> 1.01 ms at 512^3)
       if (ok) {
 #pragma unroll
-        for (int s = 0; s < E::R0; ++s) st_slot<R, N>(out + a * S::HSLOT + ((size_t)(j + s * M) * N + y) * HZ + z, u[0][s]);
+        for (int s = 0; s < E::R0; ++s) st_slot<R, N, 3>(out + a * S::HSLOT + ((size_t)(j + s * M) * N + y) * HZ + z, u[0][s]);
       }
     }
     return;
@@ -348,7 +351,7 @@ k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* _
       if (ok[k]) {
 #pragma unroll
         for (int s = 0; s < E::R0; ++s)
-          st_slot<R, N>(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], u[k][s]);
+          st_slot<R, N, 3>(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], u[k][s]);
       }
   }
 }
@@ -418,7 +421,7 @@ k_xpass_fwdinv(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
       if (ok[k]) {
 #pragma unroll
         for (int s = 0; s < E::R0; ++s)
-          st_slot<R, N>(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], u[k][s]);
+          st_slot<R, N, 3>(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], u[k][s]);
       }
   }
 }
@@ -496,7 +499,7 @@ k_xpass_lpt3(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::ty
       if (ok[k]) {
 #pragma unroll
         for (int s = 0; s < E::R0; ++s)
-          st_slot<R, N>(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], v[a][k][s]);
+          st_slot<R, N, 3>(out + a * S::HSLOT + ((size_t)(jj[k] + s * M) * N + y) * HZ + zz[k], v[a][k][s]);
       }
   }
 }
@@ -733,7 +736,7 @@ k_ypass_fwd(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::typ
   for (int k = 0; k < E::K0; ++k)
     if (ok[k]) {
 #pragma unroll
-      for (int s = 0; s < E::R0; ++s) st_slot<R, N>(out + ((size_t)x * N + jj[k] + s * M) * HZ + zz[k], v[k][s]);
+      for (int s = 0; s < E::R0; ++s) st_slot<R, N, 2>(out + ((size_t)x * N + jj[k] + s * M) * HZ + zz[k], v[k][s]);
     }
 }
 
@@ -990,8 +993,8 @@ k_zpass(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R>::t
       const V a = V{R(0.5) * (zk.x + zn.x), R(0.5) * (zk.y - zn.y)};   // (Z_k + conj Z_{N-k})/2
       const V b = V{R(0.5) * (zk.y + zn.y), R(0.5) * (zn.x - zk.x)};   // (Z_k - conj Z_{N-k})/(2i)
       const int l0 = blockIdx.x * P + 2 * u;
-      if (l0 < Z::LINES) st_slot<R, N>(out + (size_t)l0 * HZ + k, a);
-      if (l0 + 1 < Z::LINES) st_slot<R, N>(out + (size_t)(l0 + 1) * HZ + k, b);
+      if (l0 < Z::LINES) st_slot<R, N, 2>(out + (size_t)l0 * HZ + k, a);
+      if (l0 + 1 < Z::LINES) st_slot<R, N, 2>(out + (size_t)(l0 + 1) * HZ + k, b);
     }
   }
 }
