@@ -1018,7 +1018,11 @@ k_zpass(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R>::t
 // running maximum f has f - delta/2 > 0.7 |T| keeps it: the 1.2% of slack covers the float32
 // rounding of T's norm and of F.  21% of the points are left for the model (counted as above), too
 // spread out for whole waves to skip it (68% of the 64-point rows hold one), so each wave gathers
-// those of its points in LDS and evaluates them densely, 64 at a time.
+// those of its points in LDS and evaluates them densely, 64 at a time.  With the model in place at
+// every point its 1230 of 1879 VALU instructions per wave bounded the pass (512^3 float32: 0.91 ms);
+// now its loads do: 0.75 ms averaged over 40 radii, 0.62 at the last, 5.4 TB/s (float64: 2.28 ->
+// 1.68 ms; 256^3 float32 with v_max: 0.222 -> 0.150 ms).  Nothing may spill: 32 bytes a lane of
+// scratch wrote 0.5 GB per launch at 512^3 and cost the whole gain (0.96 ms).
 struct ZCollapseArgs {
   const void* F;       // running F_max (R) before this batch
   void* Fout;          // F_max after it; with groups, [groups][N^3]
@@ -1083,6 +1087,8 @@ struct ZCollapse {
   static constexpr size_t GATHER_BYTES = WHOLE ? (size_t)WAVES * GATHER * 6 * sizeof(R) : 0;
   static constexpr size_t LDS_BYTES = E::LDS_ELEMS * sizeof(V) > GATHER_BYTES ? E::LDS_ELEMS * sizeof(V) : GATHER_BYTES;
   static_assert(E::K0 == 1 && ZT::QL == 1, "z pass: one butterfly per transform per thread");
+  // least waves per SIMD: the most that hold the three transforms without spilling (float32: 114
+  // VGPRs at 512^3; lines with a radix-3 stage hold 9 values a thread, 139)
   static constexpr int WPE = sizeof(R) == 8 ? (VEL ? 1 : 2) : (VEL || E::max_held() > 8 ? 3 : 4);
 };
 

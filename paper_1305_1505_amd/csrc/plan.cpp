@@ -247,7 +247,8 @@ void plan_reset_v(pin_plan p, void* F, uint8_t* ridx, void* vmax, hipStream_t s)
 }
 
 // Waves that fill the device in the z pass: two a SIMD.  Below that the radii of a batch are split
-// into groups that run side by side.
+// into groups that run side by side (64^3 float64, 16 radii: z pass 77 us in one launch; with 1024
+// wanted, half the groups, 90; with 4096 89, each group then evaluating more of its points).
 constexpr int kZWavesWanted = 2048;
 
 void plan_run_radii(pin_plan p, const void* dk, void* F, uint8_t* ridx, void* vmax, int r0, int r1, bool fresh,
