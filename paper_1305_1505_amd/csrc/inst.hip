@@ -157,12 +157,11 @@ void reset(void* F, uint8_t* ridx, hipStream_t s) {
   hipLaunchKernelGGL((k_reset<RR>), dim3(grid), dim3(block), 0, s, static_cast<RR*>(F), ridx, total);
 }
 
-void redshift(const void* F, size_t count, const GrowthArgs& g, void* z, hipStream_t s) {
+void redshift(const void* F, size_t count, const GrowthArgs* g, void* z, hipStream_t s) {
   if (count == 0) return;
   constexpr size_t span = (size_t)kRedshiftThreads * kRedshiftValues;
   const size_t need = (count + span - 1) / span, most = 512;   // two workgroups on each of 256 CUs
-  const size_t lds = (size_t)(g.f_count + g.e_count) * kBucketStride * sizeof(double);
-  hipLaunchKernelGGL((k_redshift<RR>), dim3((unsigned)(need < most ? need : most)), dim3(kRedshiftThreads), lds, s,
+  hipLaunchKernelGGL((k_redshift<RR>), dim3((unsigned)(need < most ? need : most)), dim3(kRedshiftThreads), 0, s,
                      static_cast<const RR*>(F), count, g, static_cast<RR*>(z));
 }
 

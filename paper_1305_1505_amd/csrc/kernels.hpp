@@ -1366,8 +1366,9 @@ constexpr int kRedshiftValues = 4;       // a thread's values in flight, a workg
 template <typename R>
 __global__ void __launch_bounds__(kRedshiftThreads)
 __attribute__((amdgpu_waves_per_eu(8)))
-k_redshift(const R* __restrict__ F, size_t count, GrowthArgs g, R* __restrict__ z) {
-  extern __shared__ __align__(16) double s_poly[];
+k_redshift(const R* __restrict__ F, size_t count, const GrowthArgs* __restrict__ gp, R* __restrict__ z) {
+  const GrowthArgs g = *gp;
+  __shared__ double s_poly[kMaxBuckets * kBucketStride];
   for (int i = threadIdx.x; i < (g.f_count + g.e_count) * kBucketStride; i += kRedshiftThreads) s_poly[i] = g.poly[i];
   __syncthreads();
   constexpr int SPAN = kRedshiftThreads * kRedshiftValues;

@@ -29,7 +29,9 @@ struct CollapseStep {
   double sphere_gain, vscale;
 };
 
-// Growing-mode tables of the collapse redshift, on the device (host_math.hpp: GrowthTable).
+// Growing-mode tables of the collapse redshift (host_math.hpp: GrowthTable).  The struct itself is
+// on the device too, ahead of its tables: a call recorded in a graph then reads the tables and the
+// numbers that belong to them as pin_plan_set_growth last left them.
 struct GrowthArgs {
   const double* d;
   const double* dd;
@@ -81,8 +83,8 @@ struct SizeOps {
   // the field of `seed`, mode amplitudes from the plan's table (mode_amplitudes)
   void (*grf)(void* dk, uint64_t seed, const double* amp, hipStream_t s);
   void (*reset)(void* F, uint8_t* ridx, hipStream_t s);
-  // collapse redshift of count F values (growth tables on the device, see k_redshift)
-  void (*redshift)(const void* F, size_t count, const GrowthArgs& g, void* z, hipStream_t s);
+  // collapse redshift of count F values (*g on the device, see k_redshift)
+  void (*redshift)(const void* F, size_t count, const GrowthArgs* g, void* z, hipStream_t s);
   // count reals of the plan's precision set to zero
   void (*zero)(void* p, size_t count, hipStream_t s);
   // per-point collapse model on [6][count] tensors

@@ -116,3 +116,29 @@ def test_redshift_bucket_edges(lib, om, count):
     some = np.unique(np.linspace(0, count - 1, 60).astype(int))
     for i in some:
         assert abs(growth.growth(1.0 / (1.0 + z[i]), om) * F[i] - 1.0) <= 1e-12 + 2.0 ** -52 / (1.0 + z[i]), (F[i], z[i])
+
+
+def test_redshift_graph_follows_set_growth(lib):
+    """A redshift call captured into a HIP graph reads the plan's growth tables when it runs: after
+    pin_plan_set_growth with another omega_m a replay gives that cosmology's redshifts, bit for bit
+    the eager call's."""
+    import torch
+
+    plan = lib.Plan(16, 10.0, [1.0], prec=lib.PIN_FP64)
+    plan.set_growth(0.25)
+    F = torch.tensor(np.resize(_values(7, 400), 5000), dtype=torch.float64, device="cuda")
+    z = torch.empty_like(F)
+    plan.collapse_redshift(F)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        lib.pin_collapse_redshift(plan.handle, F.data_ptr(), F.numel(), z.data_ptr(),
+                                  torch.cuda.current_stream().cuda_stream)
+    for om in (0.25, 0.7, 1.0, 0.05, 0.25):
+        plan.set_growth(om)
+        eager = plan.collapse_redshift(F)
+        z.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(z, eager), f"omega_m {om}: {int((z != eager).sum())} of {z.numel()} differ"
+    plan.close()
