@@ -1044,13 +1044,15 @@ template <typename R> __device__ __forceinline__ R collapse_of(R xx, R xy, R xz,
   }
 }
 
-// Whether a point with tensor T could reach the running maximum f.  The term added to |T|^2 keeps
-// tensors whose squares underflow; a NaN or an overflow keeps its point.
+// Whether a point with tensor T could reach the running maximum f.  The computed F follows the bound
+// only while the sixth powers of |T| in its discriminant neither overflow nor lose bits to underflow
+// (in float32 F is infinite from |T| = 2.6e6 at some points), so points with |T| above 1.4e6 (float64
+// 1.4e40) are kept, and the term added to |T|^2 keeps those below 1e-4 (1e-40); a NaN keeps its point.
 template <typename R> __device__ __forceinline__ bool may_reach(R xx, R xy, R xz, R yy, R yz, R zz, R f) {
   const R off = xy * xy + xz * xz + yz * yz;
-  const R norm2 = (sizeof(R) == 4 ? R(1e-30) : R(1e-200)) + R(0.49) * (xx * xx + yy * yy + zz * zz + R(2) * off);
+  const R norm2 = (sizeof(R) == 4 ? R(1e-8) : R(1e-80)) + R(0.49) * (xx * xx + yy * yy + zz * zz + R(2) * off);
   const R h = f - R(0.5) * (xx + yy + zz);
-  return !(h > R(0) && h * h > norm2);
+  return !(h > R(0) && h * h > norm2 && norm2 < (sizeof(R) == 4 ? R(1e12) : R(1e80)));
 }
 
 // Place of this lane among the lanes of mask m, counted from first.

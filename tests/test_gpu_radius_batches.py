@@ -75,3 +75,27 @@ def test_ties_keep_the_larger_radius(lib, n):
     plan.collapse_times_range(dk, F2, R2, 0, len(radii))
     assert torch.equal(F, F2) and torch.equal(R, R2)
     plan.close()
+
+
+@pytest.mark.parametrize("prec,scale", [("fp32", 1e-12), ("fp32", 3e5), ("fp32", 3e6), ("fp32", 1e9), ("fp64", 1e-62),
+                                        ("fp64", 1e39), ("fp64", 1e54)])
+@pytest.mark.parametrize("n", [24, 64])
+def test_whole_call_equals_single_radii_at_any_scale(lib, prec, scale, n):
+    """Tensors so large or small that intermediate powers of the collapse model overflow or
+    underflow (in float32 F is then infinite at some points and radii): a point may be left out only
+    where the model follows its bound, so whole calls still give what single radii give."""
+    import torch
+
+    radii = W.radii_cells(9, n / 6, 0.75)
+    plan = lib.Plan(n, 2.0 * n, radii, prec=lib.PIN_FP64 if prec == "fp64" else lib.PIN_FP32)
+    dk = plan.generate_field(61) * scale
+    F, R, v = plan.collapse_times_v(dk)
+    F1, R1, v1 = torch.empty_like(F), torch.empty_like(R), torch.empty_like(v)
+    plan.collapse_reset_v(F1, R1, v1)
+    for r in range(len(radii)):
+        plan.collapse_times_range_v(dk, F1, R1, v1, r, r + 1)
+    F2, R2 = plan.collapse_times(dk)
+    torch.cuda.synchronize()
+    for name, a, b in (("F", F, F1), ("R", R, R1), ("v", v, v1), ("F without v", F2, F1), ("R without v", R2, R1)):
+        assert torch.equal(a, b), f"{name}: {int((a != b).sum())} of {a.numel()} differ"
+    plan.close()
