@@ -1089,6 +1089,7 @@ struct ZCollapse {
   static constexpr size_t GATHER_BYTES = WHOLE ? (size_t)WAVES * GATHER * 6 * sizeof(R) : 0;
   static constexpr size_t LDS_BYTES = E::LDS_ELEMS * sizeof(V) > GATHER_BYTES ? E::LDS_ELEMS * sizeof(V) : GATHER_BYTES;
   static_assert(E::K0 == 1 && ZT::QL == 1, "z pass: one butterfly per transform per thread");
+  static_assert(T % 64 == 0, "z pass: gathered points are evaluated 64 at a time by whole waves");
   // least waves per SIMD: the most that hold the three transforms without spilling (float32: 114
   // VGPRs at 512^3; lines with a radix-3 stage hold 9 values a thread, 139)
   static constexpr int WPE = sizeof(R) == 8 ? (VEL ? 1 : 2) : (VEL || E::max_held() > 8 ? 3 : 4);
