@@ -89,7 +89,14 @@ void ypass_hess_grad(const void* in, void* out, void* gout, const void* tw, int 
 
 template <bool VEL, bool WHOLE> void zcollapse_launch(const CollapseStep& c, const ZCollapseArgs& a, hipStream_t s) {
   using Z = ZCollapse<RR, NN, VEL, WHOLE>;
-  hipLaunchKernelGGL((k_zcollapse<RR, NN, VEL, WHOLE>), dim3(Z::GRID, c.groups), dim3(Z::T), 0, s,
+  if constexpr (BatchRule<RR, NN>::MANY) {
+    if (c.nb > 1) {
+      hipLaunchKernelGGL((k_zcollapse<RR, NN, VEL, WHOLE, true>), dim3(Z::GRID, c.groups), dim3(Z::T), 0, s,
+                         static_cast<const VV*>(c.in), static_cast<const VV*>(c.tw), a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_zcollapse<RR, NN, VEL, WHOLE, false>), dim3(Z::GRID), dim3(Z::T), 0, s,
                      static_cast<const VV*>(c.in), static_cast<const VV*>(c.tw), a);
 }
 

@@ -1095,7 +1095,10 @@ struct ZCollapse {
   static constexpr int WPE = sizeof(R) == 8 ? (VEL ? 1 : 2) : (VEL || E::max_held() > 8 ? 3 : 4);
 };
 
-template <typename R, int N, bool VEL, bool WHOLE>
+// MANY: the launch takes several radii.  A launch of one stores its results as they come and holds
+// the running maximum in registers: eight range calls of one radius each, 64^3 float64 327 us with the
+// kernel of several radii (33 registers spilled) and 301 with its own, 96^3 float64 581 and 539.
+template <typename R, int N, bool VEL, bool WHOLE, bool MANY>
 __global__ void __launch_bounds__((ZCollapse<R, N, VEL, WHOLE>::T))
 __attribute__((amdgpu_waves_per_eu(ZCollapse<R, N, VEL, WHOLE>::WPE)))
 k_zcollapse(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R>::type* __restrict__ tw,
@@ -1105,7 +1108,6 @@ k_zcollapse(const typename Cplx<R>::type* __restrict__ in, const typename Cplx<R
   using E = typename Z::E;
   constexpr int P = Z::P, R0 = E::R0, M0 = N / R0;
   constexpr size_t VOL = (size_t)N * N * N, PSLOT = VOL;
-  constexpr bool MANY = BatchRule<R, N>::MANY;   // one radius a launch otherwise
   __shared__ __align__(16) unsigned char lds_bytes[Z::LDS_BYTES];
   __shared__ V s_tw[tw_elems(N)];
   V* lds = reinterpret_cast<V*>(lds_bytes);

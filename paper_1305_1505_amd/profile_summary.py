@@ -34,7 +34,7 @@ COPY_BYTES = 3 << 30          # bench.py --copy-probe copies 2^28 float32 (1 GiB
 KERNEL_PATTERNS = {
     "xpass_hessian": "k_xpass<float, {n}, 0>",
     "ypass_hessian": "k_ypass_packed<float, {n}, 0>",
-    "zpass_collapse": "k_zcollapse<float, {n}, false, true>",
+    "zpass_collapse": "k_zcollapse<float, {n}, false, true",
 }
 KERNEL_KEYS = {k: v.format(n=512) for k, v in KERNEL_PATTERNS.items()}
 
