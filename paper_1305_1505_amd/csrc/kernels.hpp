@@ -189,15 +189,21 @@ template <typename R, int N> constexpr int slots_fit(int count) {
 }
 
 // Store into a slot between two passes: plain where the SLOTS half slots that matter to its next
-// reader fit the last-level cache, streamed past the caches otherwise.  y-pass outputs count a
-// radius's 9 half slots (13 with v_max), x-pass outputs their own 3, the forward y pass's and the
-// 2LPT source's 2, the prepared input itself and the x pass's outputs.  Measured: y-pass outputs
-// plain at 192^3 float32 (9 fit), y pass 70 -> 62 us, z pass 54 -> 52, but with v_max (13 do not)
-// z pass 116 -> 138 us; x-pass outputs plain at 256^3 float32 (3 fit, 9 do not), x pass 63 -> 59 us,
+// reader fit the last-level cache, streamed past the caches otherwise.  x-pass outputs count their
+// own 3, the forward y pass's and the 2LPT source's 2, the prepared input itself and the x pass's
+// outputs.  Measured: x-pass outputs plain at 256^3 float32 (3 fit, 9 do not), x pass 63 -> 59 us,
 // y pass 139 -> 112, z pass 100 -> 121 (it waits for their write-back), collapse over 20 radii
 // 5.98 -> 5.78 ms, with v_max 8.49 -> 8.01; at 512^3 streaming is the faster (y pass 1.04 -> 1.01).
-template <typename R, int N, int SLOTS = 9, typename V> __device__ __forceinline__ void st_slot(V* p, V v) {
+template <typename R, int N, int SLOTS, typename V> __device__ __forceinline__ void st_slot(V* p, V v) {
   if constexpr (slots_fit<R, N>(SLOTS) > 0) *p = v; else st_stream(p, v);
+}
+// The packed y pass's outputs, counting a radius's 9 half slots (13 with v_max): plain only in
+// float32 with two radii's worth in the cache.  y and z pass, streamed / plain: 128^3 float32 (three
+// radii a launch) 34.1 + 50.9 / 36.4 + 46.9 us, 192^3 float32 (one radius's 9 just fit) 44.3 + 52.3 /
+// 60.0 + 48.4, 96^3 float64 (four a launch) 47.0 + 95.1 / 57.2 + 89.0, 128^3 float64 25.6 + 43.0 /
+// 28.7 + 40.0; 64^3 float64 in range calls of one radius each, 16 radii: 577 / 597 us.
+template <typename R, int N, int SLOTS, typename V> __device__ __forceinline__ void st_yout(V* p, V v) {
+  if constexpr (sizeof(R) == 4 && slots_fit<R, N>(SLOTS) > 1) *p = v; else st_stream(p, v);
 }
 
 // Streaming load, for the last read of a tile (its lines need not stay in L2).
@@ -682,7 +688,7 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
             V* second =
                 reinterpret_cast<V*>(plane + (unsigned)L::index(0, jv[k] + s * M, zv[k] + HZ) * (unsigned)sizeof(V));
             if (sgn > 0) {
-              st_slot<R, N, SLOTS>(first, u[k][s]);
+              st_yout<R, N, SLOTS>(first, u[k][s]);
               // the conjugate that a slot of one component leaves to the z pass stays an operand:
               // without it the last butterfly's products would be contracted into its sums where
               // they were not, and the gradient would round differently
@@ -691,7 +697,7 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
                 asm volatile("" ::"v"(w.x), "v"(w.y));
               }
             } else if (zv[k] > 0) {
-              st_slot<R, N, SLOTS>(second, conj(u[k][s]));
+              st_yout<R, N, SLOTS>(second, conj(u[k][s]));
             }
           }
         }
