@@ -285,7 +285,7 @@ pin_status pin_plan_kernel_time(pin_plan plan, int cls, double* total_ms, long l
  * class is idle or a new one fits the device-memory budget (idle slots of other classes are
  * evicted, least recently used first), and its whole path -- field, collapse times over its
  * radii, optionally ZA and 2LPT displacements -- is then queued on that slot's stream as one
- * captured hipGraph (cached per slot for each radius count, box and displacement choice).
+ * recorded hipGraph (cached per slot for each radius count, box and displacement choice).
  * Admitted requests therefore run concurrently; within a size class admission is first come,
  * first served.  Every request's result is computed by the same kernels with the same inputs
  * whatever else is in flight, so it is bitwise identical alone and in a mix.  All server calls

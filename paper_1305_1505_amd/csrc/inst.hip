@@ -2,6 +2,7 @@
 // Compiled once per supported (N, precision) with -DPIN_INST_N=<N> -DPIN_INST_FP64=<0|1>.
 #include "grf.hpp"
 #include "kernels.hpp"
+#include "launch.hpp"
 #include "ops.hpp"
 
 #ifndef PIN_INST_N
@@ -23,81 +24,81 @@ void prep(const void* dk, void* g0, double scale, hipStream_t s) {
   const size_t total = (size_t)NN * NN * (NN / 2);
   const int block = 256;
   const int grid = (int)((total + block - 1) / block);
-  hipLaunchKernelGGL((k_prep<RR, NN>), dim3(grid), dim3(block), 0, s, static_cast<const VV*>(dk),
-                     static_cast<VV*>(g0), (RR)scale);
+  launch(k_prep<RR, NN>, dim3(grid), dim3(block), s, static_cast<const VV*>(dk),
+         static_cast<VV*>(g0), (RR)scale);
 }
 
 void xpass(int mode, const void* dk, void* out, const void* wtab, const void* tw, double scale, int nb,
            hipStream_t s) {
   using S = Strided<RR, NN, +1>;
   if (mode == 0) {
-    hipLaunchKernelGGL((k_xpass<RR, NN, 0>), dim3(S::GRID, nb, S::SPLIT ? 3 : 1), dim3(S::T), 0, s, static_cast<const VV*>(dk),
-                       static_cast<VV*>(out), static_cast<const RR*>(wtab), static_cast<const VV*>(tw), (RR)scale);
+    launch(k_xpass<RR, NN, 0>, dim3(S::GRID, nb, S::SPLIT ? 3 : 1), dim3(S::T), s, static_cast<const VV*>(dk),
+           static_cast<VV*>(out), static_cast<const RR*>(wtab), static_cast<const VV*>(tw), (RR)scale);
   } else {
-    hipLaunchKernelGGL((k_xpass<RR, NN, 1>), dim3(S::GRID, 1, S::SPLIT ? 2 : 1), dim3(S::T), 0, s, static_cast<const VV*>(dk),
-                       static_cast<VV*>(out), static_cast<const RR*>(nullptr), static_cast<const VV*>(tw), (RR)scale);
+    launch(k_xpass<RR, NN, 1>, dim3(S::GRID, 1, S::SPLIT ? 2 : 1), dim3(S::T), s, static_cast<const VV*>(dk),
+           static_cast<VV*>(out), static_cast<const RR*>(nullptr), static_cast<const VV*>(tw), (RR)scale);
   }
 }
 
 void xpass_fwdinv(bool hess, const void* in, void* out, const void* tw, double scale, hipStream_t s) {
   using S = Strided<RR, NN, +1>;
   if (hess) {
-    hipLaunchKernelGGL((k_xpass_fwdinv<RR, NN, true>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(in),
-                       static_cast<VV*>(out), static_cast<const VV*>(tw), (RR)scale);
+    launch(k_xpass_fwdinv<RR, NN, true>, dim3(S::GRID), dim3(S::T), s, static_cast<const VV*>(in),
+           static_cast<VV*>(out), static_cast<const VV*>(tw), (RR)scale);
   } else {
-    hipLaunchKernelGGL((k_xpass_fwdinv<RR, NN, false>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(in),
-                       static_cast<VV*>(out), static_cast<const VV*>(tw), (RR)scale);
+    launch(k_xpass_fwdinv<RR, NN, false>, dim3(S::GRID), dim3(S::T), s, static_cast<const VV*>(in),
+           static_cast<VV*>(out), static_cast<const VV*>(tw), (RR)scale);
   }
 }
 
 void xpass_lpt3(const void* in, void* out, const void* tw, double scale, hipStream_t s) {
   using S = Strided<RR, NN, +1>;
-  hipLaunchKernelGGL((k_xpass_lpt3<RR, NN>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(in),
-                     static_cast<VV*>(out), static_cast<const VV*>(tw), (RR)scale);
+  launch(k_xpass_lpt3<RR, NN>, dim3(S::GRID), dim3(S::T), s, static_cast<const VV*>(in),
+         static_cast<VV*>(out), static_cast<const VV*>(tw), (RR)scale);
 }
 
 void ypass(int recipe, const void* in, void* out, const void* tw, int nb, hipStream_t s) {
   if (recipe == 0) {
     using S = Strided<RR, NN, +1>;
-    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 0>), dim3(S::GRID, nb, S::SPLIT ? YRecipe<0>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
-                       static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
+    launch(k_ypass_packed<RR, NN, 0>, dim3(S::GRID, nb, S::SPLIT ? YRecipe<0>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
+           static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
   } else if (recipe == 1) {
     using S = Strided<RR, NN, +1>;
-    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 1>), dim3(S::GRID, 1, S::SPLIT ? YRecipe<1>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
-                       static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
+    launch(k_ypass_packed<RR, NN, 1>, dim3(S::GRID, 1, S::SPLIT ? YRecipe<1>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
+           static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
   } else if (recipe == 3) {
     using S = Strided<RR, NN, +1>;
-    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 3>), dim3(S::GRID, 1, S::SPLIT ? YRecipe<3>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
-                       static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
+    launch(k_ypass_packed<RR, NN, 3>, dim3(S::GRID, 1, S::SPLIT ? YRecipe<3>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
+           static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
   } else if (recipe == 4) {
     using S = Strided<RR, NN, +1>;
-    hipLaunchKernelGGL((k_ypass_packed<RR, NN, 4>), dim3(S::GRID, 1, S::SPLIT ? YRecipe<4>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
-                       static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
+    launch(k_ypass_packed<RR, NN, 4>, dim3(S::GRID, 1, S::SPLIT ? YRecipe<4>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
+           static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
   } else {
     using S = Strided<RR, NN, -1>;
-    hipLaunchKernelGGL((k_ypass_fwd<RR, NN>), dim3(S::GRID), dim3(S::T), 0, s, static_cast<const VV*>(in),
-                       static_cast<VV*>(out), static_cast<const VV*>(tw));
+    launch(k_ypass_fwd<RR, NN>, dim3(S::GRID), dim3(S::T), s, static_cast<const VV*>(in),
+           static_cast<VV*>(out), static_cast<const VV*>(tw));
   }
 }
 
 // Hessian (3 packed slots to out) and v_max gradient (2 packed slots to gout) in one y pass.
 void ypass_hess_grad(const void* in, void* out, void* gout, const void* tw, int nb, hipStream_t s) {
   using S = Strided<RR, NN, +1>;
-  hipLaunchKernelGGL((k_ypass_packed<RR, NN, 5>), dim3(S::GRID, nb, S::SPLIT ? YRecipe<5>::Q : 1), dim3(S::T), 0, s, static_cast<const VV*>(in),
-                     static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(gout));
+  launch(k_ypass_packed<RR, NN, 5>, dim3(S::GRID, nb, S::SPLIT ? YRecipe<5>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
+         static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(gout));
 }
 
 template <bool VEL, bool WHOLE> void zcollapse_launch(const CollapseStep& c, const ZCollapseArgs& a, hipStream_t s) {
   using Z = ZCollapse<RR, NN, VEL, WHOLE>;
   if constexpr (BatchRule<RR, NN>::MANY) {
     if (c.nb > 1) {
-      hipLaunchKernelGGL((k_zcollapse<RR, NN, VEL, WHOLE, true>), dim3(Z::GRID, c.groups), dim3(Z::T), 0, s,
-                         static_cast<const VV*>(c.in), static_cast<const VV*>(c.tw), a);
+      launch(k_zcollapse<RR, NN, VEL, WHOLE, true>, dim3(Z::GRID, c.groups), dim3(Z::T), s,
+             static_cast<const VV*>(c.in), static_cast<const VV*>(c.tw), a);
       return;
     }
   }
-  hipLaunchKernelGGL((k_zcollapse<RR, NN, VEL, WHOLE, false>), dim3(Z::GRID), dim3(Z::T), 0, s,
-                     static_cast<const VV*>(c.in), static_cast<const VV*>(c.tw), a);
+  launch(k_zcollapse<RR, NN, VEL, WHOLE, false>, dim3(Z::GRID), dim3(Z::T), s,
+         static_cast<const VV*>(c.in), static_cast<const VV*>(c.tw), a);
 }
 
 void zcollapse(const CollapseStep& c, hipStream_t s) {
@@ -111,8 +112,8 @@ void zcollapse(const CollapseStep& c, hipStream_t s) {
     c.whole ? zcollapse_launch<false, true>(c, a, s) : zcollapse_launch<false, false>(c, a, s);
   if (c.groups > 1) {
     const int block = 256;
-    hipLaunchKernelGGL((k_merge<RR>), dim3((unsigned)((vol + block - 1) / block)), dim3(block), 0, s, Fg, rg, c.groups,
-                       vol, static_cast<RR*>(c.F), c.ridx, c.whole, c.fresh);
+    launch(k_merge<RR>, dim3((unsigned)((vol + block - 1) / block)), dim3(block), s, Fg, rg, c.groups,
+           vol, static_cast<RR*>(c.F), c.ridx, c.whole, c.fresh);
   }
 }
 
@@ -122,12 +123,12 @@ void zpass_store(int nc, const void* in, const void* tw, void* out, hipStream_t 
   a.nc = nc;
   if (nc == 6) {
     using Z = ZPass<RR, NN, 3, EPI_STORE>;
-    hipLaunchKernelGGL((k_zpass<RR, NN, 3, EPI_STORE>), dim3(Z::GRID), dim3(Z::T), 0, s,
-                       static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
+    launch(k_zpass<RR, NN, 3, EPI_STORE>, dim3(Z::GRID), dim3(Z::T), s,
+           static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
   } else {
     using Z = ZPass<RR, NN, 2, EPI_STORE>;
-    hipLaunchKernelGGL((k_zpass<RR, NN, 2, EPI_STORE>), dim3(Z::GRID), dim3(Z::T), 0, s,
-                       static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
+    launch(k_zpass<RR, NN, 2, EPI_STORE>, dim3(Z::GRID), dim3(Z::T), s,
+           static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
   }
 }
 
@@ -136,8 +137,8 @@ void zpass_mu2(const void* in, const void* tw, void* out_slot, void* t6, hipStre
   ZArgs a{};
   a.out = out_slot;
   a.t6 = t6;
-  hipLaunchKernelGGL((k_zpass<RR, NN, 3, EPI_MU2>), dim3(Z::GRID), dim3(Z::T), 0, s,
-                     static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
+  launch(k_zpass<RR, NN, 3, EPI_MU2>, dim3(Z::GRID), dim3(Z::T), s,
+         static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
 }
 
 void zpass_lpt3(const void* in, const void* t1, const void* tw, void* out_slots, hipStream_t s) {
@@ -145,8 +146,8 @@ void zpass_lpt3(const void* in, const void* t1, const void* tw, void* out_slots,
   ZArgs a{};
   a.out = out_slots;
   a.t6 = const_cast<void*>(t1);
-  hipLaunchKernelGGL((k_zpass<RR, NN, 3, EPI_LPT3>), dim3(Z::GRID), dim3(Z::T), 0, s,
-                     static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
+  launch(k_zpass<RR, NN, 3, EPI_LPT3>, dim3(Z::GRID), dim3(Z::T), s,
+         static_cast<const VV*>(in), static_cast<const VV*>(tw), a);
 }
 
 void grf(void* dk, uint64_t seed, const double* amp, hipStream_t s) {
@@ -154,29 +155,29 @@ void grf(void* dk, uint64_t seed, const double* amp, hipStream_t s) {
   const size_t total = (size_t)NN * NN * (NN / 2 + 1);
   const int block = 256;
   const int grid = (int)((total + block - 1) / block);
-  hipLaunchKernelGGL((k_grf<RR>), dim3(grid), dim3(block), 0, s, static_cast<VV*>(dk), NN, g);
+  launch(k_grf<RR>, dim3(grid), dim3(block), s, static_cast<VV*>(dk), NN, g);
 }
 
 void reset(void* F, uint8_t* ridx, hipStream_t s) {
   const size_t total = (size_t)NN * NN * NN;
   const int block = 256;
   const int grid = (int)((total + block - 1) / block);
-  hipLaunchKernelGGL((k_reset<RR>), dim3(grid), dim3(block), 0, s, static_cast<RR*>(F), ridx, total);
+  launch(k_reset<RR>, dim3(grid), dim3(block), s, static_cast<RR*>(F), ridx, total);
 }
 
 void redshift(const void* F, size_t count, const GrowthArgs* g, void* z, hipStream_t s) {
   if (count == 0) return;
   constexpr size_t span = (size_t)kRedshiftThreads * kRedshiftValues;
   const size_t need = (count + span - 1) / span, most = 512;   // two workgroups on each of 256 CUs
-  hipLaunchKernelGGL((k_redshift<RR>), dim3((unsigned)(need < most ? need : most)), dim3(kRedshiftThreads), 0, s,
-                     static_cast<const RR*>(F), count, g, static_cast<RR*>(z));
+  launch(k_redshift<RR>, dim3((unsigned)(need < most ? need : most)), dim3(kRedshiftThreads), s,
+         static_cast<const RR*>(F), count, g, static_cast<RR*>(z));
 }
 
 void zero(void* p, size_t count, hipStream_t s) {
   if (count == 0) return;
   const int block = 256;
   const int grid = (int)((count + block - 1) / block);
-  hipLaunchKernelGGL((k_zero<RR>), dim3(grid), dim3(block), 0, s, static_cast<RR*>(p), count);
+  launch(k_zero<RR>, dim3(grid), dim3(block), s, static_cast<RR*>(p), count);
 }
 
 void collapse_points(const void* t6, size_t count, void* F, double sphere_gain, hipStream_t s) {
@@ -184,8 +185,8 @@ void collapse_points(const void* t6, size_t count, void* F, double sphere_gain, 
   CollapseConst cc{sphere_gain};
   const int block = 256;
   const int grid = (int)((count + block - 1) / block);
-  hipLaunchKernelGGL((k_collapse_points<RR>), dim3(grid), dim3(block), 0, s, static_cast<const RR*>(t6), count,
-                     static_cast<RR*>(F), cc);
+  launch(k_collapse_points<RR>, dim3(grid), dim3(block), s, static_cast<const RR*>(t6), count,
+         static_cast<RR*>(F), cc);
 }
 
 }  // namespace

@@ -8,6 +8,7 @@
 #include <new>
 
 #include "host_math.hpp"
+#include "launch.hpp"
 
 namespace pin {
 
@@ -64,6 +65,38 @@ void hip_check(hipError_t e, const char* what) {
 
 void set_last_error(const std::string& m) { g_last_error = m; }
 const char* last_error() { return g_last_error.c_str(); }
+
+static thread_local GraphRecorder* g_recorder = nullptr;
+
+GraphRecorder* GraphRecorder::current() { return g_recorder; }
+
+GraphRecorder::GraphRecorder() {
+  if (g_recorder != nullptr) fail(PIN_ERR_DEVICE, "a graph is already being recorded on this thread");
+  hip_check(hipGraphCreate(&graph_, 0), "hipGraphCreate");
+  g_recorder = this;
+}
+
+GraphRecorder::~GraphRecorder() {
+  g_recorder = nullptr;
+  (void)hipGraphDestroy(graph_);
+}
+
+void GraphRecorder::add(const void* kernel, dim3 grid, dim3 block, void** args) {
+  hipKernelNodeParams k{};
+  k.func = const_cast<void*>(kernel);
+  k.gridDim = grid;
+  k.blockDim = block;
+  k.kernelParams = args;   // copied by the call
+  hipGraphNode_t node = nullptr;
+  hip_check(hipGraphAddKernelNode(&node, graph_, &last_, last_ != nullptr ? 1 : 0, &k), "hipGraphAddKernelNode");
+  last_ = node;
+}
+
+hipGraphExec_t GraphRecorder::instantiate() {
+  hipGraphExec_t ge = nullptr;
+  hip_check(hipGraphInstantiate(&ge, graph_, nullptr, nullptr, 0), "hipGraphInstantiate");
+  return ge;
+}
 
 void* device_alloc(size_t bytes, const char* what) {
   void* p = nullptr;

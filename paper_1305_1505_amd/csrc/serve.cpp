@@ -1,5 +1,5 @@
 // HIP executor of the serving scheduler: slots are plans plus per-request buffers and a stream;
-// a request is the field kernel followed by one captured hipGraph of the rest of its path.
+// a request is the field kernel followed by one recorded hipGraph of the rest of its path.
 #include <hip/hip_runtime.h>
 #include <rocprofiler-sdk-roctx/roctx.h>
 
@@ -7,6 +7,7 @@
 #include <map>
 #include <tuple>
 
+#include "launch.hpp"
 #include "plan.hpp"
 #include "serve_core.hpp"
 
@@ -23,7 +24,7 @@ struct HipSlot {
   uint8_t* ridx = nullptr;
   void* psi1 = nullptr;
   void* psi2 = nullptr;
-  // captured graphs by (n_radii, box, want_disp), with the launch count of their last use; at
+  // graphs by (n_radii, box, want_disp), with the launch count of their last use; at
   // most kMaxGraphs, the least recently used dropped first
   std::map<std::tuple<int, double, int>, std::pair<hipGraphExec_t, uint64_t>> graphs;
   uint64_t launches = 0;
@@ -115,7 +116,7 @@ class HipExec {
         (void)hipGraphExecDestroy(old->second.first);
         s->graphs.erase(old);
       }
-      it = s->graphs.emplace(key, std::make_pair(capture(s, want_disp), uint64_t(0))).first;
+      it = s->graphs.emplace(key, std::make_pair(record(s, want_disp), uint64_t(0))).first;
     }
     it->second.second = ++s->launches;
     hip_check(hipGraphLaunch(it->second.first, s->stream), "hipGraphLaunch");
@@ -147,25 +148,12 @@ class HipExec {
  private:
   // The seed-independent rest of the path (every radius, displacements) as one graph on the slot's
   // buffers; kernel nodes only.
-  hipGraphExec_t capture(Slot* s, int want_disp) {
+  hipGraphExec_t record(Slot* s, int want_disp) {
     pin_plan p = s->plan;
-    hip_check(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
-    try {
-      plan_run_radii(p, s->dk, s->F, s->ridx, nullptr, 0, p->nr, true, s->stream);
-      if (want_disp) plan_displacements(p, s->dk, s->psi1, s->psi2, s->stream);
-    } catch (...) {
-      hipGraph_t g = nullptr;
-      (void)hipStreamEndCapture(s->stream, &g);
-      if (g) (void)hipGraphDestroy(g);
-      throw;
-    }
-    hipGraph_t g = nullptr;
-    hip_check(hipStreamEndCapture(s->stream, &g), "hipStreamEndCapture");
-    hipGraphExec_t ge = nullptr;
-    const hipError_t e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    hip_check(e, "hipGraphInstantiate");
-    return ge;
+    GraphRecorder graph;
+    plan_run_radii(p, s->dk, s->F, s->ridx, nullptr, 0, p->nr, true, s->stream);
+    if (want_disp) plan_displacements(p, s->dk, s->psi1, s->psi2, s->stream);
+    return graph.instantiate();
   }
 
   pin_serve_config cfg_;

@@ -322,7 +322,7 @@ class Core {
   };
 
   // Admission: requests are matched to slots under the lock; their launches (radius tables,
-  // field, graph capture on a slot's first request of a shape, graph replay) run after it is
+  // field, recording the graph on a slot's first request of a shape, graph replay) run after it is
   // released, so client calls never wait behind them.  Only this thread creates, launches and
   // destroys slots, and a slot being launched is busy with a RUNNING request, so nothing else
   // touches it meanwhile.

@@ -149,3 +149,47 @@ def test_small_budget_serialises_and_completes(lib):
         assert e.value.status == B.PIN_ERR_BUDGET
     finally:
         B.pin_serve_destroy(srv)
+
+
+def test_copies_of_other_threads_while_graphs_are_recorded(lib):
+    """The server records a graph for each new kind of request, on its own thread.  Copies that other
+    threads of the process make meanwhile on the default stream must not fail, nor the requests."""
+    import ctypes
+    import threading
+
+    import torch
+
+    B = lib
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipMemcpy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
+    src = torch.arange(64, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    dst = np.empty(64, dtype=np.int32)
+    stop, codes = threading.Event(), []
+
+    def copier():
+        while not stop.is_set():
+            codes.append(hip.hipMemcpy(dst.ctypes.data, src.data_ptr(), dst.nbytes, 2))   # device -> host
+
+    srv = B.pin_serve_create(B.make_serve_config(4e9, max_slots_per_class=2))
+    th = threading.Thread(target=copier)
+    th.start()
+    try:
+        # each radius count is another graph
+        reqs = [dict(seed=70 + i, n=16, box=32.0, radii=W.radii_cells(3 + i, 4.0, 0.75), disp=1) for i in range(24)]
+        served = []
+        for r in reqs:
+            t = B.pin_serve_submit(srv, B.make_request(r["seed"], r["n"], r["box"], r["radii"], r["disp"]))
+            st, res = B.pin_serve_wait(srv, t, 60.0)
+            served.append((st, _served(lib, res, r) if st == B.PIN_OK else None))
+            B.pin_serve_release(srv, t)
+    finally:
+        stop.set()
+        th.join()
+        B.pin_serve_destroy(srv)
+    assert len(codes) > 24 and set(codes) == {0}
+    assert np.array_equal(dst, np.arange(64))
+    for r, (st, got) in zip(reqs, served):
+        assert st == B.PIN_OK
+        for a, b in zip(got, _plain(lib, r)):
+            assert np.array_equal(a, b)
