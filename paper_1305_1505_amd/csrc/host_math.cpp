@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <system_error>
 #include <thread>
 
 namespace pin {
@@ -184,6 +185,23 @@ std::vector<double> radius_ladder(int n, double box, double r_max, double r_min,
 
 namespace {
 
+// f(first, last) over consecutive parts of [0, count), one per host thread up to eight; the calling
+// thread takes the first part and those that no thread could be started for.
+template <typename F> void in_parts(int count, const F& f) {
+  const int parts = std::max(1, std::min(8, (int)std::thread::hardware_concurrency()));
+  auto edge = [=](int k) { return (int)((long long)count * k / parts); };
+  std::vector<std::thread> threads;
+  threads.reserve((size_t)parts);
+  int k = 1;
+  try {
+    for (; k < parts; ++k) threads.emplace_back([&f, edge, k] { f(edge(k), edge(k + 1)); });
+  } catch (const std::system_error&) {
+  }
+  f(0, edge(1));
+  if (k < parts) f(edge(k), count);
+  for (auto& t : threads) t.join();
+}
+
 // 1 + z_c at F from the table: the node interval holding t = 1/F, then Newton steps on the cubic
 // Hermite interpolant of D(y) there.
 double one_plus_z(const GrowthTable& g, double F) {
@@ -234,12 +252,12 @@ void redshift_buckets(GrowthTable& g, double om, double ol, double d_inf) {
   const int n = kBucketCoefs;
   g.poly.assign((size_t)(g.f_count + g.e_count) * kBucketStride, std::nan(""));
   const double half = 0.5 / (1 << kBucketBits);
-  for (int k = 0; k < g.f_count + g.e_count; ++k) {
+  auto fit = [&](int k) {
     const bool in_f = k < g.f_count;
     const int id = in_f ? g.f_base + k : g.e_base + k - g.f_count;
     const double lo = bucket_start(id), octave = std::exp2(std::floor(std::log2(lo))), mid = lo / octave + half;
     auto value = [&](double u) { return one_plus_z(g, (mid + u) * octave + (in_f ? 0.0 : g.f_inf)); };
-    if (!(bucket_start(id + 1) + (in_f ? 0.0 : g.f_inf) < top) || !(lo + (in_f ? 0.0 : g.f_inf) > last)) continue;
+    if (!(bucket_start(id + 1) + (in_f ? 0.0 : g.f_inf) < top) || !(lo + (in_f ? 0.0 : g.f_inf) > last)) return;
     // divided differences at the Chebyshev points, then the monomial coefficients
     long double x[kBucketCoefs], c[kBucketCoefs], a[kBucketCoefs] = {};
     for (int i = 0; i < n; ++i) {
@@ -262,7 +280,10 @@ void redshift_buckets(GrowthTable& g, double om, double ol, double d_inf) {
     const double cond = in_f ? 1.0 : std::fmin(1.0, 2.0 * lo / (lo + g.f_inf));
     if (err * cond <= 8e-13)
       for (int j = 0; j < n; ++j) g.poly[(size_t)k * kBucketStride + j] = (double)a[j];
-  }
+  };
+  in_parts(g.f_count + g.e_count, [&](int lo, int hi) {
+    for (int k = lo; k < hi; ++k) fit(k);
+  });
 }
 
 }  // namespace
@@ -288,9 +309,25 @@ GrowthTable growth_table(double om) {
   };
   const double ys = std::log(1e-8);
   double I = 0.4 * std::pow(1e-8, 2.5) * std::pow(om, -1.5);   // leading term below a = 1e-8
-  // up to the first node, then node by node (four panels per interval)
-  const int pre = 4000;
-  for (int p = 0; p < pre; ++p) I += panel(ys + (g.y0 - ys) * p / pre, ys + (g.y0 - ys) * (p + 1) / pre);
+  // panels up to the first node, node by node (four per interval) and from the first node to a = 1:
+  // independent, so evaluated on several threads, and summed in order
+  const int pre = 4000, at = pre + 4 * (kGrowthNodes - 1), p1 = 4000;
+  std::vector<double> part((size_t)at + p1);
+  in_parts(at + p1, [&](int lo, int hi) {
+    for (int k = lo; k < hi; ++k) {
+      if (k < pre) {
+        part[k] = panel(ys + (g.y0 - ys) * k / pre, ys + (g.y0 - ys) * (k + 1) / pre);
+      } else if (k < at) {
+        const int q = (k - pre) % 4;
+        const double ya = g.y0 + (k - pre) / 4 * g.h;
+        part[k] = panel(ya + g.h * q / 4, ya + g.h * (q + 1) / 4);
+      } else {
+        const int p = k - at;
+        part[k] = panel(g.y0 * (1.0 - (double)p / p1), g.y0 * (1.0 - (double)(p + 1) / p1));
+      }
+    }
+  });
+  for (int p = 0; p < pre; ++p) I += part[p];
   auto d_unnorm = [&](double a, double Ia) { return 2.5 * om * std::sqrt(om / (a * a * a) + ol) * Ia; };
   auto dd_unnorm = [&](double a, double Ia) {   // a dD/da
     const double e = std::sqrt(om / (a * a * a) + ol);
@@ -299,23 +336,23 @@ GrowthTable growth_table(double om) {
   std::vector<double> Iy(kGrowthNodes);
   Iy[0] = I;
   for (int i = 1; i < kGrowthNodes; ++i) {
-    const double ya = g.y0 + (i - 1) * g.h;
-    for (int q = 0; q < 4; ++q) I += panel(ya + g.h * q / 4, ya + g.h * (q + 1) / 4);
+    for (int q = 0; q < 4; ++q) I += part[pre + 4 * (i - 1) + q];
     Iy[i] = I;
   }
   // normalisation at a = 1 (y = 0)
   double I1 = Iy[0];
-  const int p1 = 4000;
-  for (int p = 0; p < p1; ++p) I1 += panel(g.y0 * (1.0 - (double)p / p1), g.y0 * (1.0 - (double)(p + 1) / p1));
+  for (int p = 0; p < p1; ++p) I1 += part[at + p];
   const double norm = d_unnorm(1.0, I1);
   g.a_per_D = norm;
   g.d.resize(kGrowthNodes);
   g.dd.resize(kGrowthNodes);
-  for (int i = 0; i < kGrowthNodes; ++i) {
-    const double a = std::exp(g.y0 + i * g.h);
-    g.d[i] = d_unnorm(a, Iy[i]) / norm;
-    g.dd[i] = dd_unnorm(a, Iy[i]) / norm;
-  }
+  in_parts(kGrowthNodes, [&](int lo, int hi) {
+    for (int i = lo; i < hi; ++i) {
+      const double a = std::exp(g.y0 + i * g.h);
+      g.d[i] = d_unnorm(a, Iy[i]) / norm;
+      g.dd[i] = dd_unnorm(a, Iy[i]) / norm;
+    }
+  });
   g.guide_l0 = std::log2(g.d[0]);
   const double hl = (std::log2(g.d[kGrowthNodes - 1]) - g.guide_l0) / (kGrowthGuide - 1);
   g.guide_inv = 1.0 / hl;
