@@ -81,7 +81,8 @@ int pin_size_supported(int n);
 
 /* Device bytes pin_plan_create allocates for `desc` (workspace, tables); host only.  On small grids
  * the collapse passes take several radii a launch and the workspace holds that many radii's slots
- * (up to 256 MB); where that much memory is not free, pin_plan_create takes one radius's. */
+ * (up to 256 MB).  Where what that adds is more than a 16th of the free device memory, or cannot be
+ * had, pin_plan_create takes one radius's, and so does the first _v call. */
 pin_status pin_plan_workspace_bytes(const pin_plan_desc* desc, size_t* bytes);
 
 /* Validate `desc` without touching the GPU. */

@@ -136,6 +136,20 @@ int collapse_batch(int n, int n_radii, bool fp64, bool vel) {
 
 static size_t xslots(int batch) { return batch > 1 ? 3 * (size_t)batch : 4; }
 
+// Device memory for several radii a launch, or null where one radius's has to do: `extra` is what it
+// takes beyond that.  Speed is all it gives, so it is taken only while it is a small part of what is
+// free (a 16th), and the plan's later workspaces and the program's own find the room they would find
+// beside a plan of one radius a launch.
+static void* batch_alloc(size_t bytes, size_t extra) {
+  size_t free_bytes = 0, total = 0;
+  void* p = nullptr;
+  if (hipMemGetInfo(&free_bytes, &total) == hipSuccess && extra <= free_bytes / 16 &&
+      hipMalloc(&p, bytes) == hipSuccess)
+    return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+
 size_t workspace_bytes(int n, int n_radii, bool fp64, int batch) {
   const size_t rb = fp64 ? 8 : 4;
   const size_t slot = (size_t)n * n * (n / 2) * 2 * rb;
@@ -201,21 +215,16 @@ pin_plan plan_create(const pin_plan_desc* desc, int radii_capacity, int batch) {
     p->slot_bytes = (size_t)p->n * p->n * (p->n / 2) * p->complex_bytes();
     p->tw = device_alloc((size_t)p->n * p->complex_bytes(), "twiddles");
     p->wtab = device_alloc((size_t)p->n * (p->nr_capacity + 1) * p->real_bytes, "windows");
-    p->batch = batch;
-    if (batch > 1 && (hipMalloc(&p->X, xslots(batch) * p->slot_bytes) != hipSuccess ||
-                      hipMalloc(&p->Y, 6 * batch * p->slot_bytes) != hipSuccess)) {
-      (void)hipGetLastError();
-      if (p->X) (void)hipFree(p->X);
-      p->X = p->Y = nullptr;
-      p->batch = 1;
-    }
-    if (p->X == nullptr) {
-      p->X = device_alloc(4 * p->slot_bytes, "workspace X");
-      p->Y = device_alloc(6 * p->slot_bytes, "workspace Y");
-    }
-    p->G = device_alloc(p->slot_bytes, "workspace G");
-    upload(p->tw, twiddles(p->n), p->fp64, nullptr);
     (void)amp_table(p);
+    // G, X and Y last, as one block: freeing one of 80 MB and more takes 0.23 ms (of 40 MB 0.01)
+    const auto slots = [](int b) { return 1 + xslots(b) + 6 * (size_t)b; };
+    if (batch > 1) p->W = batch_alloc(slots(batch) * p->slot_bytes, (slots(batch) - slots(1)) * p->slot_bytes);
+    p->batch = p->W != nullptr ? batch : 1;
+    if (p->W == nullptr) p->W = device_alloc(slots(1) * p->slot_bytes, "workspace");
+    p->G = p->W;
+    p->X = static_cast<char*>(p->W) + p->slot_bytes;
+    p->Y = static_cast<char*>(p->X) + xslots(p->batch) * p->slot_bytes;
+    upload(p->tw, twiddles(p->n), p->fp64, nullptr);
     upload(p->window_row(p->nr_capacity), std::vector<double>((size_t)p->n, 1.0), p->fp64, nullptr);
     plan_set_radii(p, desc->radii_cells, desc->n_radii, nullptr);
   } catch (...) {
@@ -236,9 +245,7 @@ void plan_free(pin_plan p) {
   if (p->tw) (void)hipFree(p->tw);
   for (auto& t : p->amp_tables) (void)hipFree(t.second);
   if (p->wtab) (void)hipFree(p->wtab);
-  if (p->X) (void)hipFree(p->X);
-  if (p->Y) (void)hipFree(p->Y);
-  if (p->G) (void)hipFree(p->G);
+  if (p->W) (void)hipFree(p->W);
   if (p->V) (void)hipFree(p->V);
   if (p->L) (void)hipFree(p->L);
   fragment_free(p->frag);
@@ -287,8 +294,16 @@ constexpr int kZWavesWanted = 2048;
 void plan_run_radii(pin_plan p, const void* dk, void* F, uint8_t* ridx, void* vmax, int r0, int r1, bool fresh,
                     hipStream_t s) {
   const bool vel = vmax != nullptr;
-  const int most = vel && p->ops->batch_v < p->batch ? p->ops->batch_v : p->batch;
-  if (vel && p->V == nullptr) p->V = device_alloc(velocity_workspace_bytes(p->n, p->fp64, most), "workspace V");
+  if (vel && p->V == nullptr) {
+    const size_t one = velocity_workspace_bytes(p->n, p->fp64, 1);
+    p->batch_v = p->ops->batch_v < p->batch ? p->ops->batch_v : p->batch;
+    if (p->batch_v > 1) p->V = batch_alloc(p->batch_v * one, (p->batch_v - 1) * one);
+    if (p->V == nullptr) {
+      p->batch_v = 1;
+      p->V = device_alloc(one, "workspace V");
+    }
+  }
+  const int most = vel ? p->batch_v : p->batch;
   prep_hessian_input(p, dk, s);
   const int batches = (r1 - r0 + most - 1) / most;
   for (int k = 0; k < batches; ++k) {

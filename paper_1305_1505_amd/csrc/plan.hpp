@@ -95,10 +95,12 @@ struct pin_plan_s {
   std::vector<std::pair<double, void*>> amp_tables;
   void* wtab = nullptr;   // (nr_capacity + 1) rows of N window values
   int batch = 1;          // radii per launch of the collapse passes (collapse_batch)
+  int batch_v = 1;        // the same with v_max, once V is there
+  void* W = nullptr;      // the block that holds G, X and Y
   void* X = nullptr;      // max(4, 3 batch) half slots
   void* Y = nullptr;      // 6 half slots (= 3 packed slots) per radius of the batch
   void* G = nullptr;      // 1 half slot: the radius-independent Hessian input
-  void* V = nullptr;      // 4 half slots (= 2 packed slots) per radius for v_max, allocated on first use
+  void* V = nullptr;      // 4 half slots (= 2 packed slots) per radius of batch_v, allocated on first use
   pin::FragWorkspace frag;  // fragmentation workspace, allocated on first use
   void* L = nullptr;      // 10 half slots for the third-order displacement, allocated on first use:
                           // T1 as six real fields, then four source slots
