@@ -47,6 +47,23 @@ struct GaussLegendre {
   }
 };
 
+// f(first, last) over consecutive parts of [0, count), one per host thread up to eight; the calling
+// thread takes the first part and those that no thread could be started for.
+template <typename F> void in_parts(int count, const F& f) {
+  const int parts = std::max(1, std::min(8, (int)std::thread::hardware_concurrency()));
+  auto edge = [=](int k) { return (int)((long long)count * k / parts); };
+  std::vector<std::thread> threads;
+  threads.reserve((size_t)parts);
+  int k = 1;
+  try {
+    for (; k < parts; ++k) threads.emplace_back([&f, edge, k] { f(edge(k), edge(k + 1)); });
+  } catch (const std::system_error&) {
+  }
+  f(0, edge(1));
+  if (k < parts) f(edge(k), count);
+  for (auto& t : threads) t.join();
+}
+
 }  // namespace
 
 double bbks_transfer(double k, double gamma) {
@@ -67,19 +84,23 @@ double sigma2_tophat_unit(double radius, double gamma, double ns) {
   const double a = std::log(1e-7), b = std::log(1e3);
   const int panels = 4000;
   const double h = (b - a) / panels;
-  double total = 0.0;
-  for (int p = 0; p < panels; ++p) {
-    const double mid = a + (p + 0.5) * h;
-    double s = 0.0;
-    for (int i = 0; i < 16; ++i) {
-      const double lnk = mid + 0.5 * h * gl.x[i];
-      const double k = std::exp(lnk);
-      const double t = bbks_transfer(k, gamma);
-      const double w = tophat_window(k * radius);
-      s += gl.w[i] * k * k * k * std::pow(k, ns) * t * t * w * w;
+  std::vector<double> part(panels);
+  in_parts(panels, [&](int lo, int hi) {
+    for (int p = lo; p < hi; ++p) {
+      const double mid = a + (p + 0.5) * h;
+      double s = 0.0;
+      for (int i = 0; i < 16; ++i) {
+        const double lnk = mid + 0.5 * h * gl.x[i];
+        const double k = std::exp(lnk);
+        const double t = bbks_transfer(k, gamma);
+        const double w = tophat_window(k * radius);
+        s += gl.w[i] * k * k * k * std::pow(k, ns) * t * t * w * w;
+      }
+      part[p] = s;
     }
-    total += 0.5 * h * s;
-  }
+  });
+  double total = 0.0;
+  for (int p = 0; p < panels; ++p) total += 0.5 * h * part[p];
   return total / (2.0 * kPi * kPi);
 }
 
@@ -184,23 +205,6 @@ std::vector<double> radius_ladder(int n, double box, double r_max, double r_min,
 }
 
 namespace {
-
-// f(first, last) over consecutive parts of [0, count), one per host thread up to eight; the calling
-// thread takes the first part and those that no thread could be started for.
-template <typename F> void in_parts(int count, const F& f) {
-  const int parts = std::max(1, std::min(8, (int)std::thread::hardware_concurrency()));
-  auto edge = [=](int k) { return (int)((long long)count * k / parts); };
-  std::vector<std::thread> threads;
-  threads.reserve((size_t)parts);
-  int k = 1;
-  try {
-    for (; k < parts; ++k) threads.emplace_back([&f, edge, k] { f(edge(k), edge(k + 1)); });
-  } catch (const std::system_error&) {
-  }
-  f(0, edge(1));
-  if (k < parts) f(edge(k), count);
-  for (auto& t : threads) t.join();
-}
 
 // 1 + z_c at F from the table: the node interval holding t = 1/F, then Newton steps on the cubic
 // Hermite interpolant of D(y) there.

@@ -23,3 +23,16 @@ def test_growth_table_takes_less_than_its_quadrature_on_one_thread(tmp_path):
     if len(os.sched_getaffinity(0)) < 2:
         pytest.skip("one CPU: nothing to share the work with")
     assert float(table) < float(quadrature), (table, quadrature)
+
+
+def test_sigma8_quadrature_takes_less_than_on_one_thread(tmp_path):
+    """Nearly all of pin_plan_create on a small grid is the sigma_8 quadrature."""
+    csrc = os.path.join(ROOT, "paper_1305_1505_amd", "csrc")
+    exe = str(tmp_path / "sigma_table")
+    subprocess.run(["g++", "-std=c++17", "-O3", "-pthread", "-I", csrc, os.path.join(ROOT, "tests", "native", "sigma_table.cpp"),
+                    os.path.join(csrc, "host_math.cpp"), "-o", exe], check=True, capture_output=True)
+    worst, parts, one = (float(x) for x in subprocess.run([exe], check=True, capture_output=True, text=True).stdout.split())
+    assert worst <= 1e-9        # the integrand is smooth over 64000 steps, but oscillates beyond k R = 2000
+    if len(os.sched_getaffinity(0)) < 2:
+        pytest.skip("one CPU: nothing to share the work with")
+    assert parts < 0.7 * one, (parts, one)
