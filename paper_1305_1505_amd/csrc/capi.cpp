@@ -1,9 +1,10 @@
 // C ABI of libpin (include/pin.h): argument validation around the plan operations of plan.cpp.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
-#include <cstring>
 #include <initializer_list>
+#include <memory>
 #include <vector>
 
 #include "pin.h"
@@ -152,23 +153,18 @@ pin_status pin_plan_set_growth(pin_plan plan, double omega_m, hipStream_t stream
     check_plan(plan);
     if (!(omega_m > 0.0 && omega_m <= 1.0)) fail(PIN_ERR_INVALID_ARG, "omega_m must be in (0, 1]");
     const GrowthTable g = growth_table(omega_m);
-    // one block: its GrowthArgs, D, dD/dy, the polynomials' space, the guide
-    const size_t na = (sizeof(GrowthArgs) + 255) / 256 * 256, nd = (size_t)kGrowthNodes * sizeof(double),
-                 np = (size_t)kMaxBuckets * kBucketStride * sizeof(double), ng = g.guide.size() * sizeof(int32_t);
-    std::vector<unsigned char> bytes(na + 2 * nd + np + ng);
-    if (plan->growth == nullptr) plan->growth = device_alloc(bytes.size(), "growth table");
-    const double* d = reinterpret_cast<const double*>(static_cast<const char*>(plan->growth) + na);
-    const double* poly = d + 2 * kGrowthNodes;
-    const GrowthArgs args{d, d + kGrowthNodes, kGrowthNodes, g.y0, g.h, g.a_per_D, g.lambda_over_m,
-                          reinterpret_cast<const int32_t*>(poly + (size_t)kMaxBuckets * kBucketStride), kGrowthGuide,
-                          (float)g.guide_l0, (float)g.guide_inv, poly, g.f_base, g.f_count, g.e_base, g.e_count,
-                          g.f_inf, g.f_none};
-    std::memcpy(bytes.data(), &args, sizeof args);
-    std::memcpy(bytes.data() + na, g.d.data(), nd);
-    std::memcpy(bytes.data() + na + nd, g.dd.data(), nd);
-    if (!g.poly.empty()) std::memcpy(bytes.data() + na + 2 * nd, g.poly.data(), g.poly.size() * sizeof(double));
-    std::memcpy(bytes.data() + na + 2 * nd + np, g.guide.data(), ng);
-    hip_check(hipMemcpyAsync(plan->growth, bytes.data(), bytes.size(), hipMemcpyHostToDevice, stream),
+    if (plan->growth == nullptr)
+      plan->growth = static_cast<GrowthTables*>(device_alloc(sizeof(GrowthTables), "growth tables"));
+    const GrowthTables* t = plan->growth;   // device addresses, not read here
+    const auto host = std::make_unique<GrowthTables>();
+    host->args = GrowthArgs{t->d, t->dd, kGrowthNodes, g.y0, g.h, g.a_per_D, g.lambda_over_m, t->guide, kGrowthGuide,
+                            (float)g.guide_l0, (float)g.guide_inv, g.f_base, g.f_count, g.e_base, g.e_count, g.f_inf,
+                            g.f_none};
+    std::copy(g.poly.begin(), g.poly.end(), host->poly);
+    std::copy(g.d.begin(), g.d.end(), host->d);
+    std::copy(g.dd.begin(), g.dd.end(), host->dd);
+    std::copy(g.guide.begin(), g.guide.end(), host->guide);
+    hip_check(hipMemcpyAsync(plan->growth, host.get(), sizeof(GrowthTables), hipMemcpyHostToDevice, stream),
               "hipMemcpyAsync");
     hip_check(hipStreamSynchronize(stream), "hipStreamSynchronize");
   });
@@ -182,8 +178,7 @@ pin_status pin_collapse_redshift(pin_plan plan, const void* F, size_t count, voi
     if (count > ((size_t)1 << 40)) fail(PIN_ERR_INVALID_ARG, "count is too large");
     check_device_range(F, count * plan->real_bytes, "F");
     check_device_range(zc, count * plan->real_bytes, "zc");
-    const GrowthArgs* g = static_cast<const GrowthArgs*>(plan->growth);
-    plan->launch(KC_REDSHIFT, stream, [&] { plan->ops->redshift(F, count, g, zc, stream); });
+    plan->launch(KC_REDSHIFT, stream, [&] { plan->ops->redshift(F, count, plan->growth, zc, stream); });
   });
 }
 

@@ -165,12 +165,17 @@ void reset(void* F, uint8_t* ridx, hipStream_t s) {
   launch(k_reset<RR>, dim3(grid), dim3(block), s, static_cast<RR*>(F), ridx, total);
 }
 
-void redshift(const void* F, size_t count, const GrowthArgs* g, void* z, hipStream_t s) {
+void redshift(const void* F, size_t count, const GrowthTables* t, void* z, hipStream_t s) {
   if (count == 0) return;
+  if (count <= kRedshiftFew) {
+    launch(k_redshift_few<RR>, dim3((unsigned)((count + 255) / 256)), dim3(256), s, static_cast<const RR*>(F), count, t,
+           static_cast<RR*>(z));
+    return;
+  }
   constexpr size_t span = (size_t)kRedshiftThreads * kRedshiftValues;
   const size_t need = (count + span - 1) / span, most = 512;   // two workgroups on each of 256 CUs
   launch(k_redshift<RR>, dim3((unsigned)(need < most ? need : most)), dim3(kRedshiftThreads), s,
-         static_cast<const RR*>(F), count, g, static_cast<RR*>(z));
+         static_cast<const RR*>(F), count, t, static_cast<RR*>(z));
 }
 
 void zero(void* p, size_t count, hipStream_t s) {

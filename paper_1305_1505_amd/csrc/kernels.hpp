@@ -1336,7 +1336,7 @@ __global__ void k_reset(R* __restrict__ F, uint8_t* __restrict__ ridx, size_t co
 // D = a (1 - (2/11)(Lambda/Om) a^3 + ...) / a_per_D is inverted directly.  The search for every
 // value (a chain of dependent loads, three float64 divisions and an exponential) took 179 us for
 // the 256^3 values of a float32 grid, 0.75 TB/s of its 8 bytes a value; with the buckets 42 us,
-// 3.2 TB/s (128 us with the coefficients gathered through L1, four cache lines a value).
+// 3.2 TB/s.
 // z_c by search, for f >= f_none
 __device__ __forceinline__ double redshift_search(const GrowthArgs& g, double f) {
   const double t = 1.0 / f;
@@ -1371,16 +1371,39 @@ __device__ __forceinline__ double redshift_search(const GrowthArgs& g, double f)
   return exp(-(g.y0 + (lo + s) * g.h)) - 1.0;
 }
 
+// z_c from the buckets' polynomials, or by search for values outside them
+__device__ __forceinline__ double redshift_of(const GrowthArgs& g, const double* poly, double f) {
+  if (!(f >= g.f_none)) return -1.0;
+  // bucket of F, else of e
+  const double e = f - g.f_inf;
+  const unsigned bf = (unsigned)(__double2hiint(f) >> (20 - kBucketBits)) - (unsigned)g.f_base;
+  const unsigned be = (unsigned)(__double2hiint(e) >> (20 - kBucketBits)) - (unsigned)g.e_base;
+  const bool in_f = bf < (unsigned)g.f_count, in_e = be < (unsigned)g.e_count;
+  double out = __builtin_nan("");
+  if (in_f || in_e) {
+    const double x = in_f ? f : e;
+    const double* c = poly + kBucketStride * (in_f ? bf : g.f_count + be);
+    const int hi = (__double2hiint(x) & 0xFFFFF) | 0x3FF00000;
+    const double mid = __hiloint2double((hi & ~((1 << (20 - kBucketBits)) - 1)) | (1 << (19 - kBucketBits)), 0);
+    const double u = __hiloint2double(hi, __double2loint(x)) - mid;
+    double v = c[kBucketCoefs - 1];
+#pragma unroll
+    for (int j = kBucketCoefs - 2; j >= 0; --j) v = fma(v, u, c[j]);
+    out = v - 1.0;
+  }
+  return out == out ? out : redshift_search(g, f);
+}
+
 constexpr int kRedshiftThreads = 1024;   // two workgroups a CU: 64 KB of LDS and 64 VGPRs a thread
 constexpr int kRedshiftValues = 4;       // a thread's values in flight, a workgroup's apart
 
 template <typename R>
 __global__ void __launch_bounds__(kRedshiftThreads)
 __attribute__((amdgpu_waves_per_eu(8)))
-k_redshift(const R* __restrict__ F, size_t count, const GrowthArgs* __restrict__ gp, R* __restrict__ z) {
-  const GrowthArgs g = *gp;
+k_redshift(const R* __restrict__ F, size_t count, const GrowthTables* __restrict__ t, R* __restrict__ z) {
   __shared__ double s_poly[kMaxBuckets * kBucketStride];
-  for (int i = threadIdx.x; i < (g.f_count + g.e_count) * kBucketStride; i += kRedshiftThreads) s_poly[i] = g.poly[i];
+  for (int i = threadIdx.x; i < kMaxBuckets * kBucketStride; i += kRedshiftThreads) s_poly[i] = t->poly[i];
+  const GrowthArgs g = t->args;
   __syncthreads();
   constexpr int SPAN = kRedshiftThreads * kRedshiftValues;
 #pragma unroll 1
@@ -1393,32 +1416,22 @@ k_redshift(const R* __restrict__ F, size_t count, const GrowthArgs* __restrict__
     }
 #pragma unroll
     for (int k = 0; k < kRedshiftValues; ++k) {
-      // bucket of F, else of e
-      const double fk = (double)f[k], e = fk - g.f_inf;
-      const unsigned bf = (unsigned)(__double2hiint(fk) >> (20 - kBucketBits)) - (unsigned)g.f_base;
-      const unsigned be = (unsigned)(__double2hiint(e) >> (20 - kBucketBits)) - (unsigned)g.e_base;
-      const bool in_f = bf < (unsigned)g.f_count, in_e = be < (unsigned)g.e_count;
-      double out = -1.0;
-      if (fk >= g.f_none) {
-        out = __builtin_nan("");
-        if (in_f || in_e) {
-          const double x = in_f ? fk : e;
-          const double* c = s_poly + kBucketStride * (in_f ? bf : g.f_count + be);
-          const int hi = (__double2hiint(x) & 0xFFFFF) | 0x3FF00000;
-          const double mid =
-              __hiloint2double((hi & ~((1 << (20 - kBucketBits)) - 1)) | (1 << (19 - kBucketBits)), 0);
-          const double u = __hiloint2double(hi, __double2loint(x)) - mid;
-          double v = c[kBucketCoefs - 1];
-#pragma unroll
-          for (int j = kBucketCoefs - 2; j >= 0; --j) v = fma(v, u, c[j]);
-          out = v - 1.0;
-        }
-        if (!(out == out)) out = redshift_search(g, fk);
-      }
+      const double out = redshift_of(g, s_poly, (double)f[k]);
       const size_t i = i0 + k * kRedshiftThreads;
       if (i < count) z[i] = (R)out;
     }
   }
+}
+
+// Few values: coefficients from memory, no fill of LDS to wait for.  float32, one call of many in a
+// graph, this / the kernel above: 1 value 1.6 / 3.0 us, 2^16 2.0 / 5.0, 2^19 5.4 / 6.9, 2^20 7.6 / 7.6,
+// 2^21 11.6 / 10.3 (the search for every value: 2.2, 4.0, 7.8, 12.3, 21.0).
+constexpr size_t kRedshiftFew = 1 << 19;
+template <typename R>
+__global__ void __launch_bounds__(256)
+k_redshift_few(const R* __restrict__ F, size_t count, const GrowthTables* __restrict__ t, R* __restrict__ z) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < count) z[i] = (R)redshift_of(t->args, t->poly, (double)F[i]);
 }
 
 template <typename R>

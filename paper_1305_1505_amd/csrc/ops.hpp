@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "host_math.hpp"
+
 namespace pin {
 
 struct LaunchShape {
@@ -29,9 +31,7 @@ struct CollapseStep {
   double sphere_gain, vscale;
 };
 
-// Growing-mode tables of the collapse redshift (host_math.hpp: GrowthTable).  The struct itself is
-// on the device too, ahead of its tables: a call recorded in a graph then reads the tables and the
-// numbers that belong to them as pin_plan_set_growth last left them.
+// Growing-mode tables of the collapse redshift (host_math.hpp: GrowthTable).
 struct GrowthArgs {
   const double* d;
   const double* dd;
@@ -40,9 +40,16 @@ struct GrowthArgs {
   const int32_t* guide;   // last node with d <= 2^(l0 + b / inv), per bucket b < k
   int k;
   float l0, inv;
-  const double* poly;     // kBucketStride values per bucket: f_count of F, then e_count of e
   int f_base, f_count, e_base, e_count;
   double f_inf, f_none;
+};
+// All of it on the device: a call recorded in a graph reads the tables and the numbers that belong to
+// them as pin_plan_set_growth last left them.
+struct GrowthTables {
+  GrowthArgs args;
+  double poly[kMaxBuckets * kBucketStride];   // kBucketStride values per bucket: f_count of F, then e_count of e
+  double d[kGrowthNodes], dd[kGrowthNodes];
+  int32_t guide[kGrowthGuide];
 };
 
 struct SizeOps {
@@ -83,8 +90,8 @@ struct SizeOps {
   // the field of `seed`, mode amplitudes from the plan's table (mode_amplitudes)
   void (*grf)(void* dk, uint64_t seed, const double* amp, hipStream_t s);
   void (*reset)(void* F, uint8_t* ridx, hipStream_t s);
-  // collapse redshift of count F values (*g on the device, see k_redshift)
-  void (*redshift)(const void* F, size_t count, const GrowthArgs* g, void* z, hipStream_t s);
+  // collapse redshift of count F values (*t on the device, see k_redshift)
+  void (*redshift)(const void* F, size_t count, const GrowthTables* t, void* z, hipStream_t s);
   // count reals of the plan's precision set to zero
   void (*zero)(void* p, size_t count, hipStream_t s);
   // per-point collapse model on [6][count] tensors

@@ -104,7 +104,7 @@ struct pin_plan_s {
   pin::FragWorkspace frag;  // fragmentation workspace, allocated on first use
   void* L = nullptr;      // 10 half slots for the third-order displacement, allocated on first use:
                           // T1 as six real fields, then four source slots
-  void* growth = nullptr; // GrowthArgs and its tables after pin_plan_set_growth
+  pin::GrowthTables* growth = nullptr;   // on the device, after pin_plan_set_growth
   size_t slot_bytes = 0;
   bool timing = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> events[pin::KC_COUNT];

@@ -128,7 +128,7 @@ void zpass_mu2(const void*, const void*, void* out, void*, hipStream_t) { need(o
 void zpass_lpt3(const void*, const void*, const void*, void* out, hipStream_t) { need(out, 4 * half()); }
 void grf(void*, uint64_t, const double*, hipStream_t) {}
 void reset(void*, uint8_t*, hipStream_t) {}
-void redshift(const void*, size_t, const GrowthArgs*, void*, hipStream_t) {}
+void redshift(const void*, size_t, const GrowthTables*, void*, hipStream_t) {}
 void zero(void*, size_t, hipStream_t) {}
 void collapse_points(const void*, size_t, void*, double, hipStream_t) {}
 

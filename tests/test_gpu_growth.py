@@ -142,3 +142,25 @@ def test_redshift_graph_follows_set_growth(lib):
         torch.cuda.synchronize()
         assert torch.equal(z, eager), f"omega_m {om}: {int((z != eager).sum())} of {z.numel()} differ"
     plan.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_redshift_does_not_depend_on_the_count(lib, prec):
+    """The same values give the same bits in a call of few (coefficients from memory), of more than
+    2^19 (from LDS) and of so many that each workgroup takes a second turn (above 512 x 4096)."""
+    import torch
+
+    p = lib.PIN_FP64 if prec == "fp64" else lib.PIN_FP32
+    plan = lib.Plan(16, 10.0, [1.0], prec=p)
+    plan.set_growth(0.3)
+    limit = 1.0 / growth.growth_limit(0.3)
+    values = np.concatenate([_values(9, 3000), limit * (1 + np.geomspace(1e-9, 1.0, 1500)), [np.inf, np.nan, 1e30, limit]])
+    base = torch.tensor(values, device="cuda").to(plan.real)
+    m = base.numel()
+    few = plan.collapse_redshift(base)
+    for count in (1 << 19, (1 << 19) + 1, 512 * 4096 + 4097, 3 * 512 * 4096 - 1):
+        F = base.repeat(count // m + 1)[:count]
+        z = plan.collapse_redshift(F)
+        want = few.repeat(count // m + 1)[:count]
+        assert torch.equal(z, want), f"count {count}: {int((z != want).sum())} differ"
+    plan.close()
