@@ -57,35 +57,29 @@ void xpass_lpt3(const void* in, void* out, const void* tw, double scale, hipStre
          static_cast<VV*>(out), static_cast<const VV*>(tw), (RR)scale);
 }
 
+template <int RECIPE> void ypass_packed(const void* in, void* out, void* out2, const void* tw, int nb, hipStream_t s) {
+  using S = Strided<RR, NN, +1>;
+  launch(k_ypass_packed<RR, NN, RECIPE>, dim3(S::GRID, nb, S::SPLIT ? YRecipe<RECIPE>::Q : 1), dim3(S::T), s,
+         static_cast<const VV*>(in), static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(out2));
+}
+
 void ypass(int recipe, const void* in, void* out, const void* tw, int nb, hipStream_t s) {
   if (recipe == 0) {
-    using S = Strided<RR, NN, +1>;
-    launch(k_ypass_packed<RR, NN, 0>, dim3(S::GRID, nb, S::SPLIT ? YRecipe<0>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
-           static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
+    ypass_packed<0>(in, out, nullptr, tw, nb, s);
   } else if (recipe == 1) {
-    using S = Strided<RR, NN, +1>;
-    launch(k_ypass_packed<RR, NN, 1>, dim3(S::GRID, 1, S::SPLIT ? YRecipe<1>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
-           static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
-  } else if (recipe == 3) {
-    using S = Strided<RR, NN, +1>;
-    launch(k_ypass_packed<RR, NN, 3>, dim3(S::GRID, 1, S::SPLIT ? YRecipe<3>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
-           static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
+    ypass_packed<1>(in, out, nullptr, tw, nb, s);
   } else if (recipe == 4) {
-    using S = Strided<RR, NN, +1>;
-    launch(k_ypass_packed<RR, NN, 4>, dim3(S::GRID, 1, S::SPLIT ? YRecipe<4>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
-           static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(nullptr));
+    ypass_packed<4>(in, out, nullptr, tw, nb, s);
   } else {
     using S = Strided<RR, NN, -1>;
-    launch(k_ypass_fwd<RR, NN>, dim3(S::GRID), dim3(S::T), s, static_cast<const VV*>(in),
-           static_cast<VV*>(out), static_cast<const VV*>(tw));
+    launch(k_ypass_fwd<RR, NN>, dim3(S::GRID), dim3(S::T), s, static_cast<const VV*>(in), static_cast<VV*>(out),
+           static_cast<const VV*>(tw));
   }
 }
 
 // Hessian (3 packed slots to out) and v_max gradient (2 packed slots to gout) in one y pass.
 void ypass_hess_grad(const void* in, void* out, void* gout, const void* tw, int nb, hipStream_t s) {
-  using S = Strided<RR, NN, +1>;
-  launch(k_ypass_packed<RR, NN, 5>, dim3(S::GRID, nb, S::SPLIT ? YRecipe<5>::Q : 1), dim3(S::T), s, static_cast<const VV*>(in),
-         static_cast<VV*>(out), static_cast<const VV*>(tw), static_cast<VV*>(gout));
+  ypass_packed<5>(in, out, gout, tw, nb, s);
 }
 
 template <bool VEL, bool WHOLE> void zcollapse_launch(const CollapseStep& c, const ZCollapseArgs& a, hipStream_t s) {

@@ -300,8 +300,8 @@ k_xpass(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::type* _
         u[0][s] = cscale(val, powf_int(R(ifreq(n, N)), a));
       }
       E::run(u, lds, s_tw, t);
-      // outputs streamed past the caches: left there, their dirty lines would be written back
-      // while the y pass runs (y pass 1.04 -> 1.01 ms at 512^3)
+      // streamed past the caches on large grids (st_slot): left there, their dirty lines would be
+      // written back while the y pass runs
       if (ok) {
 #pragma unroll
         for (int s = 0; s < E::R0; ++s) st_slot<R, N, 3>(out + a * S::HSLOT + ((size_t)(j + s * M) * N + y) * HZ + z, u[0][s]);
@@ -518,11 +518,10 @@ k_xpass_lpt3(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::ty
 //   Hessian (RECIPE 0), packed order xy xz | yy yz | xx zz:
 //       (1,1,0) (1,0,1) | (0,2,0) (0,1,1) | (2,0,0) (0,0,2)
 //   gradient (RECIPE 1), packed order x y | z:  (1,0,0) (0,1,0) | (0,0,1)
-//   gradient of the Hessian's x-pass outputs (RECIPE 3, v_max): RECIPE 1's components times i,
-//       which the gradient x pass applies itself but the Hessian x pass does not (TI)
 //   three finished components (RECIPE 4, the third-order displacement), packed order x y | z:
 //       (0,0,0) (1,0,0) | (2,0,0)
-//   Hessian and v_max gradient in one pass (RECIPE 5): RECIPE 0's pairs, then RECIPE 3's into a
+//   Hessian and v_max gradient in one pass (RECIPE 5): RECIPE 0's pairs, then RECIPE 1's components
+//       times i, which the gradient x pass applies itself but the Hessian x pass does not (TI), into a
 //       second output (pairs from SPLIT on), so the Hessian x-pass outputs are read once
 // The z pass maps the packed order back to (xx, xy, xz, yy, yz, zz) and (x, y, z).
 // STREAM: the last transform that reads an input tile streams it (its lines need not stay in L2).
@@ -538,9 +537,6 @@ template <> struct YRecipe<1> {
   static constexpr int NIN = 2, NC = 3, Q = 2, SPLIT = 0;
   static constexpr int A[3] = {1, 0, 0}, B[3] = {0, 1, 0}, C[3] = {0, 0, 1};
   static constexpr bool ti(int) { return false; }
-};
-template <> struct YRecipe<3> : YRecipe<1> {
-  static constexpr bool ti(int) { return true; }
 };
 template <> struct YRecipe<4> {
   static constexpr bool STREAM = true;
@@ -620,7 +616,7 @@ k_ypass_packed(const typename Cplx<R>::type* __restrict__ in, typename Cplx<R>::
   // One transform per (pair, sign): u = fy^bA fz^cA X_aA + sgn i fy^bB fz^cB X_aB.  By
   // linearity sgn = +1 gives C[kz] = A + iB and sgn = -1 gives conj(C[N - kz]) = A - iB.  Each
   // transform reads its inputs itself (L2 hits after the first read of a tile) so that only one
-  // transform's data is live and two workgroups fit on a CU; the outputs are streamed past L2.
+  // transform's data is live and two workgroups fit on a CU; outputs as st_yout says.
 #pragma unroll
   for (int q = 0; q < RC::Q; ++q) {
     if (S::SPLIT && q != (int)blockIdx.z) continue;

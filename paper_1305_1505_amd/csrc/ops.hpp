@@ -68,10 +68,10 @@ struct SizeOps {
   // fused forward-x / inverse-x of the third-order displacement: four source slots -> three
   void (*xpass_lpt3)(const void* in, void* out, const void* tw, double scale, hipStream_t s);
   // y pass: recipe 0 Hessian (3 half slots -> 3 packed slots), 1 gradient (2 half -> 2 packed),
-  // 2 forward (1 half -> 1 half), 3 gradient times i from the Hessian x pass (2 half -> 2 packed),
-  // 4 three finished components (3 half -> 2 packed); nb radii (recipes 0 and 1), one otherwise
+  // 2 forward (1 half -> 1 half, nb = 1), 4 three finished components (3 half -> 2 packed); nb radii,
+  // the slots of one behind the other's
   void (*ypass)(int recipe, const void* in, void* out, const void* tw, int nb, hipStream_t s);
-  // Hessian y pass that also writes the v_max gradient (y recipe 3's slots) to gout
+  // Hessian y pass that also writes the v_max gradient (2 packed slots per radius) to gout
   void (*ypass_hess_grad)(const void* in, void* out, void* gout, const void* tw, int nb, hipStream_t s);
   // z pass (packed slots in) with the collapse epilogue over a batch of radii, and v_max if gin is
   // not null; with several groups, `part` takes each group's result and a second launch merges them
