@@ -25,11 +25,13 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+COPY_GBS = 5100.0        # a 1 GiB device copy (read + write), what a pass can hope for
 
 
 def algorithmic_bytes(cls, n, real_bytes):
-    """Bytes a launch of kernel class `cls` must move at grid size n: its input and output workspace
-    slots (a slot is one N x N x N/2 complex array) and, for the collapse pass, F and the radius index."""
+    """Bytes a launch of kernel class `cls` moves at grid size n if it takes one radius by itself and
+    every point changes: its input and output workspace slots (a slot is one N x N x N/2 complex array)
+    and, for the collapse pass, F and the radius index."""
     cb = 2 * real_bytes
     slot = n * n * (n // 2) * cb          # one workspace slot (kz = N/2 plane not stored)
     vol = n ** 3
@@ -38,6 +40,24 @@ def algorithmic_bytes(cls, n, real_bytes):
         "ypass_hessian": 3 * slot + 6 * slot,             # 3 in, 6 out
         "zpass_collapse": 6 * slot + vol * (2 * real_bytes + 1),   # 6 in; F read + F, ridx written
     }.get(cls)
+
+
+def pass_bytes(cls, n, real_bytes, radii, launches, calls):
+    """Bytes that `launches` launches of kernel class `cls`, which took `radii` radii in `calls` whole
+    calls, had to move together: the slots of every radius and, for the collapse pass, F read by each
+    launch but a call's first, F and the radius index written once a call (later radii write them only
+    where they change)."""
+    slot, vol = n * n * (n // 2) * 2 * real_bytes, n ** 3
+    if cls == "zpass_collapse":
+        return 6 * slot * radii + vol * real_bytes * (launches - calls) + vol * (real_bytes + 1) * calls
+    if algorithmic_bytes(cls, n, real_bytes) is None:
+        return None
+    return algorithmic_bytes(cls, n, real_bytes) * radii
+
+
+def limiter(bytes_per_s, valu_issue_frac):
+    """What holds a kernel back, of memory (its rate against a copy's) and VALU issue, if known."""
+    return "valu" if valu_issue_frac is not None and valu_issue_frac > bytes_per_s / (COPY_GBS * 1e9) else "hbm"
 
 
 def measured_traffic(cls, n, prec):
@@ -326,7 +346,7 @@ def collapse_leg(B, W, n, box, radii, prec, seed):
     passes = {}
     for k in ("xpass_hessian", "ypass_hessian", "zpass_collapse"):
         # a launch takes several radii on small grids
-        by = algorithmic_bytes(k, n, real_bytes) * len(radii) // kt[k]["launches"]
+        by = pass_bytes(k, n, real_bytes, len(radii), kt[k]["launches"], 1) // kt[k]["launches"]
         gbs = by / (kt[k]["avg_ms"] * 1e-3) / 1e9
         passes[k] = {"avg_ms": round(kt[k]["avg_ms"], 4), "bytes_per_launch": by, "GB/s": round(gbs, 1),
                      "frac": round(gbs / HBM_PEAK_GBS, 4)}
@@ -423,15 +443,21 @@ def main():
 
     # per-kernel durations: HIP events around every launch, on the stream the kernels run on, in
     # steps of their own after the timed region (the events stay out of ms_per_step)
-    kernels = kernel_times(B, plan, step, max(1, min(args.steps, 3)))
+    reps = max(1, min(args.steps, 3))
+    kernels = kernel_times(B, plan, step, reps)
+    # bytes per launch: a launch takes several radii on small grids, and the 2LPT source is one more
+    # transform of the Hessian's x and y passes
+    launch_bytes = {k: pass_bytes(k, n, real_bytes, reps * (len(radii) + (k != "zpass_collapse")), v["launches"], reps)
+                    for k, v in kernels.items()}
+    launch_bytes = {k: by // kernels[k]["launches"] for k, by in launch_bytes.items() if by}
 
     # the dominant kernel of the path: largest summed time among the three per-radius passes
     dom = max(("xpass_hessian", "ypass_hessian", "zpass_collapse"), key=lambda k: kernels[k]["total_ms"])
-    dom_bytes = algorithmic_bytes(dom, n, real_bytes)
+    dom_bytes = launch_bytes[dom]
     achieved = dom_bytes / (kernels[dom]["avg_ms"] * 1e-3) / 1e9
     measured = measured_traffic(dom, n, prec)
-    # priced against HBM: its bytes are the pass's floor
-    roofline = {"bound": "hbm", "kernel": dom, "limiter": "hbm",
+    # priced against HBM: the bytes of the pass's slots
+    roofline = {"bound": "hbm", "kernel": dom,
                 "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": round(measured["bytes"]) if measured else None,
@@ -440,9 +466,10 @@ def main():
     # one wave64 instruction per 4 cycles per SIMD at 2.4 GHz) over its measured launch time
     issue_ns = measured_issue(dom, n, prec)
     roofline["valu_issue_frac"] = round(issue_ns / (kernels[dom]["avg_ms"] * 1e6), 4) if issue_ns else None
+    moved = measured["bytes"] if measured else dom_bytes
+    roofline["limiter"] = limiter(moved / (kernels[dom]["avg_ms"] * 1e-3), roofline["valu_issue_frac"])
     per_kernel = {k: {"avg_ms": round(v["avg_ms"], 4), "launches": v["launches"],
-                      "GB/s": (round(algorithmic_bytes(k, n, real_bytes) / (v["avg_ms"] * 1e-3) / 1e9, 1)
-                               if algorithmic_bytes(k, n, real_bytes) else None)}
+                      "GB/s": round(launch_bytes[k] / (v["avg_ms"] * 1e-3) / 1e9, 1) if k in launch_bytes else None}
                   for k, v in kernels.items()}
 
     # the path's parts on their own (HIP events on the plan's stream, which is torch's current
@@ -498,12 +525,15 @@ def main():
     B.pin_lpt3_displacement(plan.handle, dk.data_ptr(), p3.data_ptr(), stream)
     lpt3_ms = timed(lambda: B.pin_lpt3_displacement(plan.handle, dk.data_ptr(), p3.data_ptr(), stream))
     del p3
-    # whole-path roofline at the collapse-only rate: algorithmic bytes per grid-point x radius
-    # update of these passes (19 workspace slots of 4 B per point plus F read/write and the
-    # index) and the floor of any out-of-core 3D FFT design (spectrum once, one 3-component
-    # transpose round trip, F and index: 7 slots + 10 B)
+    # whole-path roofline at the collapse-only rate: bytes per grid-point x radius update of these
+    # passes (19 workspace slots of 4 B per point, F and the index as pass_bytes counts them) and of a
+    # 3D FFT that moves the spectrum once and one 3-component transpose round trip a radius (7 slots),
+    # F and the index once a call.  Both count whole slots, also where a radius's window is zero.
     slot_pp = 2 * real_bytes * (n // 2) / n   # workspace slot bytes per grid point
-    per_update = {"three_pass": 19 * slot_pp + 2 * real_bytes + 1, "floor": 7 * slot_pp + 2 * real_bytes + 2}
+    z_launches = kernels["zpass_collapse"]["launches"] // reps
+    three_pass = sum(pass_bytes(k, n, real_bytes, len(radii), z_launches, 1)
+                     for k in ("xpass_hessian", "ypass_hessian", "zpass_collapse"))
+    per_update = {"three_pass": three_pass / updates, "floor": 7 * slot_pp + (real_bytes + 1) / len(radii)}
     rate = updates / (collapse_ms * 1e-3)
     path_roofline = {k: {"bytes_per_update": round(v, 2), "GB/s": round(rate * v / 1e9, 1),
                          "frac": round(rate * v / 1e9 / HBM_PEAK_GBS, 4)} for k, v in per_update.items()}

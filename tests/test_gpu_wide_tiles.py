@@ -8,7 +8,6 @@ import math
 
 import pytest
 
-
 pytestmark = [pytest.mark.gpu, pytest.mark.timeout(300)]
 
 

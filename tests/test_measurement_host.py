@@ -91,6 +91,26 @@ def test_algorithmic_bytes_at_512():
     assert bench.algorithmic_bytes("zpass_collapse", 512, 8) == 6 * 2 * c + 512 ** 3 * 17
 
 
+def test_pass_bytes_of_whole_calls():
+    slot, vol = 512 * 512 * 256 * 8, 512 ** 3
+    # 40 launches of a radius each: F is read by all but the first, F and the index written once
+    z = bench.pass_bytes("zpass_collapse", 512, 4, 40, 40, 1)
+    assert z == 40 * 6 * slot + 39 * 4 * vol + 5 * vol
+    assert z / (40 * vol) == pytest.approx(28.025)
+    assert bench.pass_bytes("xpass_hessian", 512, 4, 41, 41, 1) == 41 * 4 * slot
+    # 64^3: 16 radii in one launch, three calls; the bytes per launch are the batch's
+    slot, vol = 64 * 64 * 32 * 16, 64 ** 3
+    assert bench.pass_bytes("ypass_hessian", 64, 8, 48, 3, 3) // 3 == 16 * 9 * slot
+    assert bench.pass_bytes("zpass_collapse", 64, 8, 48, 3, 3) // 3 == 16 * 6 * slot + 9 * vol
+    assert bench.pass_bytes("grf", 64, 8, 48, 3, 3) is None
+
+
+def test_limiter_is_the_larger_share():
+    assert bench.limiter(4.0e12, 0.9) == "valu"
+    assert bench.limiter(5.0e12, 0.81) == "hbm"
+    assert bench.limiter(1.0e12, None) == "hbm"
+
+
 def test_committed_counters_are_used_only_for_their_sources(monkeypatch):
     from paper_1305_1505_amd import binding as B
 
