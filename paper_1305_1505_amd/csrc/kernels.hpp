@@ -1065,8 +1065,8 @@ __device__ __forceinline__ unsigned lane_rank(unsigned long long m, unsigned fir
 // Radii that share a launch of the collapse passes.  The launches of a small grid are short (at
 // 64^3 a pass over one radius took 8-9 us, of which its data needs 1-2), so as many radii share one
 // as keep the slots between the passes, 9 half slots a radius, within the last-level cache.  At
-// 128^3 float32, 32 radii: 2 radii a launch 1.40 ms, 3 (this rule) 1.32, 4 1.43; 96^3 float64, 24
-// radii: 2 a launch 1.42 ms, 4 (this rule) 1.24, 5 1.25.
+// 128^3 float32, 32 radii: 2 radii a launch 1.24 ms, 3 (this rule) 1.13, 4 1.25; 96^3 float64, 24
+// radii: 2 a launch 1.29 ms, 4 (this rule) 1.05, 5 0.99 (one launch of each pass fewer).
 template <typename R, int N> struct BatchRule {
   static constexpr int most(int fit) { return fit < 1 ? 1 : fit < 16 ? fit : 16; }
   static constexpr int RADII = most(slots_fit<R, N>(9));
@@ -1092,8 +1092,8 @@ struct ZCollapse {
   static constexpr size_t LDS_BYTES = E::LDS_ELEMS * sizeof(V) > GATHER_BYTES ? E::LDS_ELEMS * sizeof(V) : GATHER_BYTES;
   static_assert(E::K0 == 1 && ZT::QL == 1, "z pass: one butterfly per transform per thread");
   static_assert(T % 64 == 0, "z pass: gathered points are evaluated 64 at a time by whole waves");
-  // least waves per SIMD: the most that hold the three transforms without spilling (float32: 114
-  // VGPRs at 512^3; lines with a radix-3 stage hold 9 values a thread, 139)
+  // least waves per SIMD: the most that hold the three transforms with at most a few registers
+  // spilled (float32: 110 VGPRs at 512^3; lines with a radix-3 stage hold 9 values a thread, 138)
   static constexpr int WPE = sizeof(R) == 8 ? (VEL ? 1 : 2) : (VEL || E::max_held() > 8 ? 3 : 4);
 };
 
