@@ -150,7 +150,9 @@ pin_status pin_collapse_times_v(pin_plan plan, const void* dk, void* F, uint8_t*
  * pin_plan_set_growth tabulates D for a flat LambdaCDM universe without radiation,
  * D(a) ~ E(a) Int_0^a da'/(a' E(a'))^3 with E^2 = omega_m a^-3 + 1 - omega_m (0 < omega_m <= 1;
  * 1 is Einstein-de Sitter, D = a), in float64 on the host, and keeps it on the device with the
- * plan (stream-ordered upload; returns when done).  pin_collapse_redshift writes, for each of
+ * plan (stream-ordered upload; returns when done; work queued earlier on other streams must not be
+ * using the plan's tables).  A pin_collapse_redshift recorded in a graph reads the tables that are
+ * there when it is replayed.  pin_collapse_redshift writes, for each of
  * count values F (device, plan precision), the redshift z_c with D(z_c) = 1/F to zc (device, plan
  * precision); z_c = -1 where F <= 0 or where 1/F is beyond D(a = 1e6) (no collapse).  Computed
  * in float64 (relative error of 1 + z_c below 1e-12, besides the rounding of z_c itself).

@@ -1092,8 +1092,9 @@ struct ZCollapse {
   static constexpr size_t LDS_BYTES = E::LDS_ELEMS * sizeof(V) > GATHER_BYTES ? E::LDS_ELEMS * sizeof(V) : GATHER_BYTES;
   static_assert(E::K0 == 1 && ZT::QL == 1, "z pass: one butterfly per transform per thread");
   static_assert(T % 64 == 0, "z pass: gathered points are evaluated 64 at a time by whole waves");
-  // least waves per SIMD: the most that hold the three transforms with at most a few registers
-  // spilled (float32: 110 VGPRs at 512^3; lines with a radix-3 stage hold 9 values a thread, 138)
+  // least waves per SIMD: the most that hold one radius's three transforms with few registers spilled
+  // (float32: 110 VGPRs at 512^3; lines with a radix-3 stage hold 9 values a thread, 138).  Launches
+  // of several radii hold more: up to 33 spilled in float64 range calls at 64^3.
   static constexpr int WPE = sizeof(R) == 8 ? (VEL ? 1 : 2) : (VEL || E::max_held() > 8 ? 3 : 4);
 };
 
